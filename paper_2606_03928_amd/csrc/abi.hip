@@ -43,8 +43,8 @@ size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// score under an order map: the score's own workspace, then the unpooled
-// per-slot scores and value scores that order_scores puts into temporal order
+// score under an order map: the score's own workspace, then room for two fp32
+// per slot (the value scores per slot, which the pooling puts into temporal order)
 size_t score_map_phys_offset(int dtype, int n_inst, int K, int B, int d, int G, int w) {
   return align256(vase::score_plan(dtype, n_inst, K, B, d, G, w).bytes);
 }
@@ -137,34 +137,17 @@ int score_common(const void* k_cache, const void* v_cache, const void* q_win, co
   const long long blocks = (long long)n_inst * plan.n_slab * (plan.n_chunk1 > plan.n_chunk2 ? plan.n_chunk1 : plan.n_chunk2);
   if (blocks > 0x7fffffffLL) return VASE_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // under an order map: unpooled scores per physical slot into the workspace,
-  // then pooled in temporal order; the value scores of the rows are permuted
+  // under an order map: pooled over temporal ranks, the value scores permuted
   // the same way (random ones are drawn per temporal rank directly)
-  const bool rows_scored = value_kind <= VASE_VALUE_VAR;
-  if (ord && plan.pool_in_kernel) {
-    // one workgroup holds each instance: it pools through the map itself
-    hipError_t e = vase::launch_score(k_cache, v_cache, q_win, dtype, n_inst, K, B, d, G, w, pool,
-                                      value_kind, lse_win, attn_out, vrange_out, ws, plan, s, ord,
-                                      dec, status);
-    if (e == hipSuccess && value_kind == VASE_VALUE_RANDOM)
-      e = vase::launch_value_random(n_inst, inst_base, K, seed, round, vrange_out, s);
-    return hip_status(e);
-  }
-  float* attn_k = attn_out;
-  float* vr_k = vrange_out;
-  if (ord) {
-    char* phys = static_cast<char*>(ws) + score_map_phys_offset(dtype, n_inst, K, B, d, G, w);
-    attn_k = reinterpret_cast<float*>(phys);
-    if (rows_scored) vr_k = reinterpret_cast<float*>(phys + align256((size_t)n_inst * K * sizeof(float)));
-  }
-  hipError_t e = vase::launch_score(k_cache, v_cache, q_win, dtype, n_inst, K, B, d, G, w,
-                                    ord ? 1 : pool, value_kind, lse_win, attn_k, vr_k, ws, plan, s,
-                                    nullptr, dec, status);
+  float* vr_phys = nullptr;
+  if (ord && !plan.pool_in_kernel)
+    vr_phys = reinterpret_cast<float*>(static_cast<char*>(ws) +
+                                       score_map_phys_offset(dtype, n_inst, K, B, d, G, w));
+  hipError_t e = vase::launch_score(k_cache, v_cache, q_win, dtype, n_inst, K, B, d, G, w, pool,
+                                    value_kind, lse_win, attn_out, vrange_out, ws, plan, s, ord,
+                                    dec, status, vr_phys);
   if (e == hipSuccess && value_kind == VASE_VALUE_RANDOM)
     e = vase::launch_value_random(n_inst, inst_base, K, seed, round, vrange_out, s);
-  if (e == hipSuccess && ord)
-    e = vase::launch_order_scores(attn_k, rows_scored ? vr_k : nullptr, ord, n_inst, K, pool,
-                                  attn_out, vrange_out, s);
   return hip_status(e);
 }
 

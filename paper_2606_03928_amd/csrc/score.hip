@@ -938,6 +938,75 @@ __global__ __launch_bounds__(kSBlock) void score_pool_kernel(const float* __rest
   attn[(size_t)inst * K + i] = s / fp;
 }
 
+// The same under an order map, by one workgroup per instance: the slots' means
+// (over the slabs, then / R) go to LDS in slot order, the map gathers them into
+// temporal order there, and the box filter runs over ranks; the value scores
+// that the score wrote per slot are gathered the same way.  Every global access
+// is in order, so it is bound by its bytes (4 per slab, 12 for the map and the
+// result, 8 more with value scores); gathering slot means from global memory
+// in a kernel behind the pooling took 50 us at 512 instances of 8192
+// candidates and two slabs, against 27 here.
+constexpr int kPoolMapPer = 8;   // candidates per thread: K <= VASE_MAX_K at 1024 threads
+template <int NT>
+__global__ __launch_bounds__(NT) void score_pool_map_kernel(
+    const float* __restrict__ col, const int32_t* __restrict__ ord,
+    const float* __restrict__ vr_slot, int K, int n_slab, int R, int pool,
+    float* __restrict__ attn, float* __restrict__ vrange) {
+  extern __shared__ float pool_buf[];   // [K] by slot, [K] by rank
+  float* const slot_v = pool_buf;
+  float* const rank_v = pool_buf + K;
+  const int inst = blockIdx.x;
+  const size_t base = (size_t)inst * K;
+  const float fr = (float)R, fp = (float)pool;
+  int o[kPoolMapPer];
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    const int i = threadIdx.x + u * NT;
+    o[u] = i < K ? min(max(ord[base + i], 0), K - 1) : 0;
+  }
+  float s[kPoolMapPer];
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) s[u] = 0.f;
+  for (int sl = 0; sl < n_slab; ++sl) {
+    const float* c = col + ((size_t)inst * n_slab + sl) * K;
+#pragma unroll
+    for (int u = 0; u < kPoolMapPer; ++u) {
+      const int i = threadIdx.x + u * NT;
+      if (i < K) s[u] += c[i];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    const int i = threadIdx.x + u * NT;
+    if (i < K) slot_v[i] = s[u] / fr;
+    s[u] = vr_slot && i < K ? vr_slot[base + i] : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    const int i = threadIdx.x + u * NT;
+    if (i < K) rank_v[i] = slot_v[o[u]];
+  }
+  __syncthreads();
+  const int h = pool / 2;
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    const int i = threadIdx.x + u * NT;
+    if (i >= K) continue;
+    if (vr_slot) slot_v[i] = s[u];
+    float sum = 0.f;
+    for (int t = i - h; t <= i + h; ++t) sum += t >= 0 && t < K ? rank_v[t] : 0.f;
+    attn[base + i] = sum / fp;
+  }
+  if (!vr_slot) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    const int i = threadIdx.x + u * NT;
+    if (i < K) vrange[base + i] = slot_v[o[u]];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // value score of each of the K candidate value rows (fp32 caches): Range,
 // L2 or Var as in chunk_value
@@ -1130,37 +1199,49 @@ hipError_t launch_score(const void* k, const void* v, const void* q, int dtype, 
                         int B, int d, int G, int w, int pool, int value_kind, const float* lse_win,
                         float* attn, float* vrange, void* ws, const ScorePlan& pl,
                         hipStream_t stream, const int32_t* ord, const DecLogits& dec,
-                        uint32_t* status) {
+                        uint32_t* status, float* vr_phys) {
   const int N = K + B;
   const int R = G * w;
   const float c = 1.4426950408889634f / sqrtf((float)d);
   char* wsb = static_cast<char*>(ws);
+  // where the value scores go: under a map that the pooling launch applies,
+  // per slot into the workspace first
+  float* vr_slot = ord && !pl.pool_in_kernel ? vr_phys : vrange;
   if (dtype == VASE_BF16) {
     if (d == 128)
-      launch_mfma<128>(k, v, q, n_inst, N, K, R, c, pool, value_kind, lse_win, pl, wsb, vrange,
+      launch_mfma<128>(k, v, q, n_inst, N, K, R, c, pool, value_kind, lse_win, pl, wsb, vr_slot,
                        attn, ord, dec, stream, status);
     else
-      launch_mfma<64>(k, v, q, n_inst, N, K, R, c, pool, value_kind, lse_win, pl, wsb, vrange,
+      launch_mfma<64>(k, v, q, n_inst, N, K, R, c, pool, value_kind, lse_win, pl, wsb, vr_slot,
                       attn, ord, dec, stream, status);
   } else {
     if (d == 128) launch_valu<float, 128>(k, q, n_inst, N, K, R, c, lse_win, pl, wsb, stream, status);
     else launch_valu<float, 64>(k, q, n_inst, N, K, R, c, lse_win, pl, wsb, stream, status);
   }
   const float* col = reinterpret_cast<const float*>(wsb + pl.off_col);
-  if (!pl.pool_in_kernel) {
-    hipLaunchKernelGGL(score_pool_kernel, dim3((K + kPoolTile - 1) / kPoolTile, n_inst),
-                       dim3(kSBlock), 0, stream, col, K, pl.n_slab, R, pool, attn);
-  }
   // value score of the K candidate rows (fused into pass 2 on the MFMA path;
   // random reservation scores are drawn by the caller of this function)
-  if (dtype != VASE_BF16 && value_kind <= VASE_VALUE_VAR) {
-    const int lpr = d * 4 / 16;
-    const int rpb = kSBlock / lpr;
-    const dim3 rg((K + rpb - 1) / rpb, n_inst);
-    if (d == 128) hipLaunchKernelGGL((value_kernel<float, 128>), rg, dim3(kSBlock), 0, stream,
-                                     static_cast<const float*>(v), N, K, value_kind, vrange, status);
-    else hipLaunchKernelGGL((value_kernel<float, 64>), rg, dim3(kSBlock), 0, stream,
-                            static_cast<const float*>(v), N, K, value_kind, vrange, status);
+  const bool rows_scored = value_kind <= VASE_VALUE_VAR;
+  if (dtype != VASE_BF16 && rows_scored) {
+    const hipError_t e = launch_value_rows(v, dtype, n_inst, N, K, d, value_kind, vr_slot, stream,
+                                           status);
+    if (e != hipSuccess) return e;
+  }
+  if (!pl.pool_in_kernel) {
+    if (ord) {
+      // 8 candidates per thread: four waves cover K <= 2048, sixteen the rest
+      const float* vs = rows_scored ? vr_slot : nullptr;
+      const size_t lds = 2 * sizeof(float) * (size_t)K;
+      if (K <= 256 * kPoolMapPer)
+        hipLaunchKernelGGL((score_pool_map_kernel<256>), dim3(n_inst), dim3(256), lds, stream, col,
+                           ord, vs, K, pl.n_slab, R, pool, attn, vrange);
+      else
+        hipLaunchKernelGGL((score_pool_map_kernel<1024>), dim3(n_inst), dim3(1024), lds, stream, col,
+                           ord, vs, K, pl.n_slab, R, pool, attn, vrange);
+    } else {
+      hipLaunchKernelGGL(score_pool_kernel, dim3((K + kPoolTile - 1) / kPoolTile, n_inst),
+                         dim3(kSBlock), 0, stream, col, K, pl.n_slab, R, pool, attn);
+    }
   }
   return hipGetLastError();
 }
