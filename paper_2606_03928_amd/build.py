@@ -25,7 +25,7 @@ LIB_PATH = os.path.join(PKG, "libvase.so")
 PEAKS_SOURCE = "peaks.hip"
 PEAKS_PATH = os.path.join(PKG, "libvase_peaks.so")
 
-SOURCES = ["abi.hip", "score.hip", "select.hip", "compact.hip", "decode.hip", "dkv.hip",
+SOURCES = ["abi.hip", "score.hip", "score_f32.hip", "select.hip", "compact.hip", "decode.hip", "dkv.hip",
            "quant.hip", "order.hip"]
 HEADERS = ["vase_internal.hpp"]
 ARCH = "gfx950"

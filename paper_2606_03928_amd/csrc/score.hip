@@ -10,9 +10,8 @@
 //   pool:           per slot: sum over row slabs, /R, then the P-wide box filter
 // All exponentials are base 2 with c = log2(e)/sqrt(d) folded in.  No floating
 // point atomics are used; every reduction has a fixed order.
-// bf16 caches use MFMA (v_mfma_f32_32x32x16_bf16, described below); fp32 caches
-// use a plain VALU path (one thread per row / per key) with Range as its own
-// kernel.
+// bf16 caches use MFMA on bf16 operands (v_mfma_f32_32x32x16_bf16, described
+// below); fp32 caches MFMA on fp32 operands (score_f32.hip).
 #include "vase_internal.hpp"
 #include "vase.h"
 
@@ -25,10 +24,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kSBlock = 256;
-constexpr float kFloor = -3.0e38f;  // finite stand-in for an empty maximum
-constexpr int kGenKeys = 32;        // VALU path: keys per chunk
-constexpr int kGenRows = 32;        // VALU path: rows per staging step
-constexpr int kGenBlock = 64;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
@@ -805,72 +800,6 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// VALU path (fp32 caches): one thread per row (pass 1) / per slot (pass 2)
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__device__ __forceinline__ void stage_rows(float* dst, const T* src, int row0, int nrow_valid,
-                                           int nrows) {
-  for (int e = threadIdx.x; e < nrows * D; e += blockDim.x) {
-    const int r = e / D, dd = e % D;
-    dst[r * (D + 1) + dd] = r < nrow_valid ? to_f32(src[(size_t)(row0 + r) * D + dd]) : 0.f;
-  }
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(kGenBlock) void score_rows_valu(
-    const T* __restrict__ k, const T* __restrict__ q, int N, int R, int n_chunk, int key_base,
-    float c, float2* __restrict__ part) {
-  __shared__ float kt[kGenKeys * (D + 1)];
-  __shared__ float qtile[kGenBlock * (D + 1)];
-  const int chunk = blockIdx.x, rb = blockIdx.y, inst = blockIdx.z;
-  const int key0 = key_base + chunk * kGenKeys;
-  const int nk = min(kGenKeys, N - key0);
-  const int row0 = rb * kGenBlock;
-  const int nr = min(kGenBlock, R - row0);
-  stage_rows<T, D>(kt, k + (size_t)inst * N * D, key0, nk, kGenKeys);
-  stage_rows<T, D>(qtile, q + (size_t)inst * R * D, row0, nr, kGenBlock);
-  __syncthreads();
-  const int t = threadIdx.x;
-  if (t >= nr) return;
-  float m = kFloor, l = 0.f;
-  for (int j = 0; j < nk; ++j) {
-    float s = 0.f;
-    for (int dd = 0; dd < D; ++dd) s = __builtin_fmaf(qtile[t * (D + 1) + dd], kt[j * (D + 1) + dd], s);
-    const float x = s * c;
-    const float mn = fmaxf(m, x);
-    l = l * fast_exp2(m - mn) + fast_exp2(x - mn);
-    m = mn;
-  }
-  part[((size_t)inst * n_chunk + chunk) * R + row0 + t] = make_float2(m, l);
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(kGenBlock) void score_cols_valu(
-    const T* __restrict__ k, const T* __restrict__ q, int N, int K, int R, float c,
-    const float* __restrict__ lse2, float* __restrict__ col) {
-  __shared__ float kt[kGenBlock * (D + 1)];
-  __shared__ float qtile[kGenRows * (D + 1)];
-  const int kb = blockIdx.x, inst = blockIdx.y;
-  const int key0 = kb * kGenBlock;
-  const int nk = min(kGenBlock, K - key0);
-  stage_rows<T, D>(kt, k + (size_t)inst * N * D, key0, nk, kGenBlock);
-  const int t = threadIdx.x;
-  float acc = 0.f;
-  for (int r0 = 0; r0 < R; r0 += kGenRows) {
-    const int nr = min(kGenRows, R - r0);
-    __syncthreads();
-    stage_rows<T, D>(qtile, q + (size_t)inst * R * D, r0, nr, kGenRows);
-    __syncthreads();
-    for (int r = 0; r < nr; ++r) {
-      float s = 0.f;
-      for (int dd = 0; dd < D; ++dd) s = __builtin_fmaf(kt[t * (D + 1) + dd], qtile[r * (D + 1) + dd], s);
-      acc += fast_exp2(__builtin_fmaf(s, c, -lse2[(size_t)inst * R + r0 + r]));
-    }
-  }
-  if (t < nk) col[(size_t)inst * K + key0 + t] = acc;
-}
-
-// ---------------------------------------------------------------------------
 // merge of the chunk partials: lse2_r = M + log2(sum_c l_c 2^(m_c - M))
 // ---------------------------------------------------------------------------
 // (plus, when lse_win is given, its persistent part: lse2_r <- log2(2^lse2_r + 2^(L_r log2 e))).
@@ -1008,8 +937,8 @@ __global__ __launch_bounds__(NT) void score_pool_map_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// value score of each of the K candidate value rows (fp32 caches): Range,
-// L2 or Var as in chunk_value
+// value score of each of the K candidate value rows: Range, L2 or Var as in
+// chunk_value (the stable compaction's, when it is not fused with the decode)
 // ---------------------------------------------------------------------------
 
 template <typename T, int D>
@@ -1033,26 +962,6 @@ __global__ __launch_bounds__(kSBlock) void value_kernel(const T* __restrict__ v,
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-template <typename T, int D>
-void launch_valu(const void* k, const void* q, int n_inst, int N, int K, int R, float c,
-                 const float* lse_win, const ScorePlan& pl, char* ws, hipStream_t stream,
-                 uint32_t* status) {
-  float2* part = reinterpret_cast<float2*>(ws + pl.off_part);
-  float* lse = reinterpret_cast<float*>(ws + pl.off_lse);
-  float* col = reinterpret_cast<float*>(ws + pl.off_col);
-  // row statistics over all N slots, or over the buffer only when lse_win is given
-  const int key_base = lse_win ? K : 0;
-  const int n_chunk = (N - key_base + kGenKeys - 1) / kGenKeys;
-  hipLaunchKernelGGL((score_rows_valu<T, D>), dim3(n_chunk, (R + kGenBlock - 1) / kGenBlock, n_inst),
-                     dim3(kGenBlock), 0, stream, static_cast<const T*>(k), static_cast<const T*>(q),
-                     N, R, n_chunk, key_base, c, part);
-  hipLaunchKernelGGL(score_lse_kernel, dim3((R + kSBlock - 1) / kSBlock, n_inst), dim3(kSBlock), 0,
-                     stream, part, R, n_chunk, lse_win, lse, status);
-  hipLaunchKernelGGL((score_cols_valu<T, D>), dim3((K + kGenBlock - 1) / kGenBlock, n_inst),
-                     dim3(kGenBlock), 0, stream, static_cast<const T*>(k), static_cast<const T*>(q),
-                     N, K, R, c, lse, col);
-}
 
 template <int D, int W, bool P>
 void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int N, int K, int R,
@@ -1156,12 +1065,17 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
     pl.n_chunk1 = (N + pl.split_keys - 1) / pl.split_keys;
     pl.n_chunk2 = pl.n_chunk1;
   } else {
-    pl.n_chunk1 = (N + kGenKeys - 1) / kGenKeys;
-    pl.n_chunk2 = (K + kGenBlock - 1) / kGenBlock;
-    pl.n_slab = 1;
-    pl.rows_per_slab = R;
     pl.waves = 0;
     pl.split_keys = 0;
+    // the workspace holds partials for runs of one 32-key tile and one row slab;
+    // longer runs leave room for the column sums of more slabs
+    pl.n_chunk2 = (N + kChunk - 1) / kChunk;
+    const size_t col = align256((size_t)n_inst * K * sizeof(float));
+    const size_t part = align256((size_t)n_inst * pl.n_chunk2 * R * sizeof(float2)) +
+                        align256((size_t)n_inst * R * sizeof(float));
+    score_f32_split(n_inst, N, K, R, part, pl);
+    pl.bytes = part + col;
+    return pl;
   }
   pl.off_part = 0;
   // the fused MFMA kernel needs no row partials, and pools by itself when one
@@ -1215,22 +1129,15 @@ hipError_t launch_score(const void* k, const void* v, const void* q, int dtype, 
       launch_mfma<64>(k, v, q, n_inst, N, K, R, c, pool, value_kind, lse_win, pl, wsb, vr_slot,
                       attn, ord, dec, stream, status);
   } else {
-    if (d == 128) launch_valu<float, 128>(k, q, n_inst, N, K, R, c, lse_win, pl, wsb, stream, status);
-    else launch_valu<float, 64>(k, q, n_inst, N, K, R, c, lse_win, pl, wsb, stream, status);
-  }
-  const float* col = reinterpret_cast<const float*>(wsb + pl.off_col);
-  // value score of the K candidate rows (fused into pass 2 on the MFMA path;
-  // random reservation scores are drawn by the caller of this function)
-  const bool rows_scored = value_kind <= VASE_VALUE_VAR;
-  if (dtype != VASE_BF16 && rows_scored) {
-    const hipError_t e = launch_value_rows(v, dtype, n_inst, N, K, d, value_kind, vr_slot, stream,
-                                           status);
+    const hipError_t e = launch_score_f32(k, v, q, n_inst, N, K, R, d, c, value_kind, lse_win, pl,
+                                          wsb, vr_slot, stream, status);
     if (e != hipSuccess) return e;
   }
+  const float* col = reinterpret_cast<const float*>(wsb + pl.off_col);
   if (!pl.pool_in_kernel) {
     if (ord) {
       // 8 candidates per thread: four waves cover K <= 2048, sixteen the rest
-      const float* vs = rows_scored ? vr_slot : nullptr;
+      const float* vs = value_kind <= VASE_VALUE_VAR ? vr_slot : nullptr;
       const size_t lds = 2 * sizeof(float) * (size_t)K;
       if (K <= 256 * kPoolMapPer)
         hipLaunchKernelGGL((score_pool_map_kernel<256>), dim3(n_inst), dim3(256), lds, stream, col,

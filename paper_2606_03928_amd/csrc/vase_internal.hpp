@@ -171,14 +171,14 @@ __device__ __forceinline__ uint32_t xcd_logical_block(uint32_t hw_block, uint32_
 // host-side launchers (defined in the kernel translation units)
 // ---------------------------------------------------------------------------
 struct ScorePlan {
-  int n_chunk1;     // slot ranges of the row-statistics pass (MFMA: ranges per instance)
-  int n_chunk2;     // slot ranges of the probability pass
+  int n_chunk1;     // slot ranges per instance of the row-statistics pass
+  int n_chunk2;     // bf16: of the probability pass; fp32: 32-key tiles (the grids' bound)
   int n_slab;       // query-row slabs (partial column sums per slab)
   int rows_per_slab;
-  int waves;        // MFMA: waves per workgroup (64 query rows each)
-  int split_keys;   // MFMA: slots per range (multiple of 32)
-  bool mfma;
-  bool pool_in_kernel;  // MFMA, one range and one slab per instance: no pool launch
+  int waves;        // bf16: waves per workgroup (64 query rows each)
+  int split_keys;   // bf16: slots per range (multiple of 32)
+  bool mfma;        // bf16
+  bool pool_in_kernel;  // bf16, one range and one slab per instance: no pool launch
   size_t off_part, off_lse, off_col, bytes;
 };
 ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w);
@@ -204,6 +204,14 @@ hipError_t launch_score(const void* k, const void* v, const void* q, int dtype, 
                         hipStream_t stream, const int32_t* ord = nullptr,
                         const DecLogits& dec = DecLogits(), uint32_t* status = nullptr,
                         float* vr_phys = nullptr);
+// fp32 caches (score_f32.hip): the runs and slabs of a plan (n_chunk1, n_slab,
+// rows_per_slab, offsets) within part_bytes of workspace ahead of the column
+// sums, and the two passes with the value scores (kind <= VASE_VALUE_VAR)
+void score_f32_split(int n_inst, int N, int K, int R, size_t part_bytes, ScorePlan& pl);
+hipError_t launch_score_f32(const void* k, const void* v, const void* q, int n_inst, int N, int K,
+                            int R, int d, float c, int kind, const float* lse_win,
+                            const ScorePlan& pl, char* ws, float* vrange, hipStream_t stream,
+                            uint32_t* status);
 // random reservation scores: vrange[i][j] = Philox uniform (purpose 2)
 hipError_t launch_value_random(int n_inst, uint32_t inst_base, int K, uint64_t seed,
                                uint32_t round, float* vrange, hipStream_t stream);
