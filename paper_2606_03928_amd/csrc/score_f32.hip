@@ -84,27 +84,6 @@ __device__ __forceinline__ f32x16_t tile_product(const Frag<D>& fixed, Frag<D>& 
 
 __device__ __forceinline__ int tile_row(int e, int half) { return 8 * (e / 4) + 4 * half + e % 4; }
 
-// Transpose-reduce of 16 values over the 32 lanes of each half wave: lane j of a
-// half ends with value j % 16 reduced (sum or max) over the half's lanes.
-template <bool MAX>
-__device__ __forceinline__ float treduce16(const float (&x)[16], int lane) {
-  float v[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = x[i];
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) {
-    const bool up = (lane & o) != 0;
-#pragma unroll
-    for (int i = 0; i < o; ++i) {
-      const float send = up ? v[i] : v[i + o], keep = up ? v[i + o] : v[i];
-      const float got = __shfl_xor(send, o, kWave);
-      v[i] = MAX ? fmaxf(keep, got) : keep + got;
-    }
-  }
-  const float got = __shfl_xor(v[0], 16, kWave);
-  return MAX ? fmaxf(v[0], got) : v[0] + got;
-}
-
 // Value scores of the candidate rows of one block (kinds Range, L2 and Var).
 template <int D>
 __device__ __forceinline__ void value_block(const float* v, int blk, int blocks_per_inst, int N, int K,
@@ -116,18 +95,23 @@ __device__ __forceinline__ void value_block(const float* v, int blk, int blocks_
   const int seg = (int)threadIdx.x % LPR;
   const uint4* vb = reinterpret_cast<const uint4*>(v + (size_t)inst * N * D);
   bool bad = false;
-  uint4 w[kValueIters];
+  // half of the loads in flight at a time, in a rolled loop: unrolled in full,
+  // the three kinds make 30 KB of code
+#pragma unroll 1
+  for (int i0 = 0; i0 < kValueIters; i0 += kValueIters / 2) {
+    uint4 w[kValueIters / 2];
 #pragma unroll
-  for (int it = 0; it < kValueIters; ++it)
-    w[it] = vb[(size_t)min(row0 + it * RPI, K - 1) * LPR + seg];
+    for (int i = 0; i < kValueIters / 2; ++i)
+      w[i] = vb[(size_t)min(row0 + (i0 + i) * RPI, K - 1) * LPR + seg];
 #pragma unroll
-  for (int it = 0; it < kValueIters; ++it) {
-    const int row = row0 + it * RPI;
-    float f[4];
-    Vec16<float>::unpack(w[it], f);
-    const float val = row_value_score<4, LPR>(f, kind);
-    if (row < K && seg == 0) out[(size_t)inst * K + row] = val;
-    if (status) bad |= row < K && any_nonfinite<4>(f);
+    for (int i = 0; i < kValueIters / 2; ++i) {
+      const int row = row0 + (i0 + i) * RPI;
+      float f[4];
+      Vec16<float>::unpack(w[i], f);
+      const float val = row_value_score<4, LPR>(f, kind);
+      if (row < K && seg == 0) out[(size_t)inst * K + row] = val;
+      if (status) bad |= row < K && any_nonfinite<4>(f);
+    }
   }
   if (status) block_status(status, bad, VASE_STATUS_VALUE_ROW);
 }
@@ -140,6 +124,7 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_rows_kernel(
     int K, int R, int n_inst, int n_rt, int n_run, int run_tiles, int key_base, float c,
     float2* __restrict__ part, unsigned n_score, int value_blocks, int value_kind,
     float* __restrict__ vrange, uint32_t* __restrict__ status) {
+  __shared__ float s_m[kFWaves][kTile][kTile + 1], s_l[kFWaves][kTile][kTile + 1];
   if (blockIdx.x >= n_score) {
     value_block<D>(v, (int)(blockIdx.x - n_score), value_blocks, N, K, value_kind, vrange, status);
     return;
@@ -177,12 +162,29 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_rows_kernel(
       m[e] = mn;
     }
   }
-  const float mj = treduce16<true>(m, lane);
+  // over the 32 keys of each row: through LDS, two lanes a row, in rolled loops.
+  // A small call runs this code once per launch, from a cold instruction cache:
+  // unrolled as lane exchanges it was 10 KB and 10 us of a one-tile launch.
+  float(&sm)[kTile][kTile + 1] = s_m[wave];
+  float(&sl)[kTile][kTile + 1] = s_l[wave];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) l[e] *= fast_exp2(m[e] - __shfl(mj, (lane & 32) + e, kWave));
-  const float lj = treduce16<false>(l, lane);
-  const int row = rt * kTile + tile_row(j % 16, half);
-  if (j < 16 && row < R) part[((size_t)inst * n_run + run) * R + row] = make_float2(mj, lj);
+  for (int e = 0; e < 16; ++e) {
+    sm[tile_row(e, half)][j] = m[e];
+    sl[tile_row(e, half)][j] = l[e];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  float mr = kFloor, lr = 0.f;
+#pragma unroll 4
+  for (int i = 0; i < kTile / 2; ++i) mr = fmaxf(mr, sm[j][half * (kTile / 2) + i]);
+  mr = fmaxf(mr, __shfl_xor(mr, 32, kWave));
+#pragma unroll 4
+  for (int i = 0; i < kTile / 2; ++i) {
+    const int t = half * (kTile / 2) + i;
+    lr += sl[j][t] * fast_exp2(sm[j][t] - mr);
+  }
+  lr += __shfl_xor(lr, 32, kWave);
+  const int row = rt * kTile + j;
+  if (half == 0 && row < R) part[((size_t)inst * n_run + run) * R + row] = make_float2(mr, lr);
 }
 
 // col[inst][slab][key] = sum over the slab's rows of exp2(s * c - lse2_r), with
