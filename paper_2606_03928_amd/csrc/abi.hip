@@ -50,7 +50,7 @@ size_t score_map_phys_offset(int dtype, int n_inst, int K, int B, int d, int G, 
 }
 size_t score_map_bytes(int dtype, int n_inst, int K, int B, int d, int G, int w) {
   const vase::ScorePlan pl = vase::score_plan(dtype, n_inst, K, B, d, G, w);
-  if (pl.pool_in_kernel) return pl.bytes;   // the kernel pools through the map itself
+  if (pl.bytes == 0) return 0;   // one workgroup per instance pools through the map itself
   return score_map_phys_offset(dtype, n_inst, K, B, d, G, w) +
          2 * align256((size_t)n_inst * K * sizeof(float));
 }

@@ -61,8 +61,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 //         the other half wave, and the W waves' sums meet in LDS in a fixed
 //         order.  The same stream carries the value rows for Range (slab 0).
 // With one range per instance both passes run in one kernel; otherwise pass 1
-// writes (m_r, l_r) per range, a merge kernel forms lse2_r, and pass 2 runs
-// as its own kernel.
+// writes (m_r, l_r) per range and pass 2 runs as its own kernel, whose
+// workgroups first merge the ranges of their rows.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -398,6 +398,35 @@ __device__ __forceinline__ void dec_logits_chunk(const uint4* slot, const uint4*
   }
 }
 
+// log2(2^l2 + 2^(L log2 e)): a row's normaliser with its supplied persistent part L
+__device__ __forceinline__ float add_persistent(float l2, float L) {
+  const float b = L * kLog2e;
+  const float m = fmaxf(l2, b);
+  return m + fast_log2(fast_exp2(l2 - m) + fast_exp2(b - m));
+}
+
+// lse2 of one row from its n_part partials p[i * R] = (m, l), four in flight:
+// m + log2(sum l_i 2^(m_i - m)).  Each pass-2 workgroup merges its own rows (a
+// launch for it took 6.5 to 15 us).
+__device__ __forceinline__ float merge_parts(const float2* p, int R, int n_part) {
+  float m = -INFINITY, l = 0.f;
+#pragma unroll 1
+  for (int i = 0; i < n_part; i += 4) {
+    float2 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = p[(size_t)min(i + u, n_part - 1) * R];
+      if (i + u >= n_part) x[u].y = 0.f;              // a repeat adds nothing
+    }
+    const float mn = fmaxf(fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x)), m);
+    l = l * fast_exp2(m - mn);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) l += x[u].y * fast_exp2(x[u].x - mn);
+    m = mn;
+  }
+  return m + fast_log2(l);
+}
+
 enum ScoreMode { kPass1 = 0, kPass2 = 1, kFused = 2 };
 
 // The ring and the stream state of one pass.  A pass that scores values (pass
@@ -512,7 +541,7 @@ template <int D, int W, int MODE, int DL, bool PARTIAL>
 __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     const uint4* __restrict__ k, const uint4* __restrict__ v, const uint16_t* __restrict__ q,
     int N, int K, int R, int n_slab, int n_split, int split_keys, float c, int pool, int value_kind,
-    const float* __restrict__ lse_win, float2* __restrict__ part, const float* __restrict__ lse2,
+    const float* __restrict__ lse_win, float2* __restrict__ part, int n_part,
     float* __restrict__ col, float* __restrict__ vrange, float* __restrict__ attn,
     const int32_t* __restrict__ ord, const uint4* __restrict__ qdec, int G_dec,
     float* __restrict__ dlog, int dl_stride, uint32_t* __restrict__ status) {
@@ -672,23 +701,25 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     }
     __syncthreads();
     float l2 = mj + fast_log2(lj);
-    if (single && row < R) {
-      // add the supplied persistent part: log2(2^l2 + 2^(L log2 e))
-      const float b = lse_win[(size_t)inst * R + row] * kLog2e;
-      const float m = fmaxf(l2, b);
-      l2 = m + fast_log2(fast_exp2(l2 - m) + fast_exp2(b - m));
-    }
+    if (single && row < R) l2 = add_persistent(l2, lse_win[(size_t)inst * R + row]);
     row_bad = row < R && !(l2 > -INFINITY && l2 < INFINITY);
     rowbuf[wave][half][j] = row < R ? l2 : INFINITY;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 32; ++i) rs[i] = rowbuf[wave][half][i];
   } else {
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const int row = row_base + elem_row(i, half);
-      rs[i] = row < R ? lse2[(size_t)inst * R + row] : INFINITY;   // padded rows give p = 0
+    // merge pass 1's ranges: each lane one row of its wave
+    const int row = row_base + elem_row(j, half);
+    float l2 = INFINITY;                              // padded rows give p = 0
+    if (row < R) {
+      l2 = merge_parts(part + (size_t)inst * n_part * R + row, R, n_part);
+      if (lse_win) l2 = add_persistent(l2, lse_win[(size_t)inst * R + row]);
+      row_bad = split == 0 && !(l2 > -INFINITY && l2 < INFINITY);
     }
+    rowbuf[wave][half][j] = l2;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 32; ++i) rs[i] = rowbuf[wave][half][i];
   }
 
   // ---- pass 2: column sums over the slab's rows for slots [key_lo, hi2)
@@ -797,43 +828,6 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     if (rng) vr_out[key_lo + i] = vr[i];
   }
   report();
-}
-
-// ---------------------------------------------------------------------------
-// merge of the chunk partials: lse2_r = M + log2(sum_c l_c 2^(m_c - M))
-// ---------------------------------------------------------------------------
-// (plus, when lse_win is given, its persistent part: lse2_r <- log2(2^lse2_r + 2^(L_r log2 e))).
-// Returns false when lse2_r is not finite (the normaliser is 0, infinite or NaN).
-__device__ __forceinline__ bool score_lse_row(const float2* __restrict__ part, int R, int n_chunk,
-                                              const float* __restrict__ lse_win,
-                                              float* __restrict__ lse2, int inst, int r) {
-  const float2* p = part + (size_t)inst * n_chunk * R + r;
-  float mm = p[0].x;
-  for (int ch = 1; ch < n_chunk; ++ch) mm = fmaxf(mm, p[(size_t)ch * R].x);
-  float ll = 0.f;
-  for (int ch = 0; ch < n_chunk; ++ch) {
-    const float2 v = p[(size_t)ch * R];
-    ll += v.y * fast_exp2(v.x - mm);
-  }
-  float l2 = mm + fast_log2(ll);
-  if (lse_win) {
-    const float b = lse_win[(size_t)inst * R + r] * kLog2e;
-    const float m = fmaxf(l2, b);
-    l2 = m + fast_log2(fast_exp2(l2 - m) + fast_exp2(b - m));
-  }
-  lse2[(size_t)inst * R + r] = l2;
-  return l2 > -INFINITY && l2 < INFINITY;
-}
-
-__global__ __launch_bounds__(kSBlock) void score_lse_kernel(const float2* __restrict__ part, int R,
-                                                          int n_chunk, const float* __restrict__ lse_win,
-                                                          float* __restrict__ lse2,
-                                                          uint32_t* __restrict__ status) {
-  const int inst = blockIdx.y;
-  const int r = blockIdx.x * kSBlock + threadIdx.x;
-  bool bad = false;
-  if (r < R) bad = !score_lse_row(part, R, n_chunk, lse_win, lse2, inst, r);
-  if (status) block_status(status, bad, VASE_STATUS_ROW_NORM);
 }
 
 // ---------------------------------------------------------------------------
@@ -981,7 +975,6 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
   const size_t dec_lds = dec.out ? q_lds + (size_t)dec.G * dl_stride * 4 : 0;
   const int dl_mode = !dec.out ? 0 : dl_stride > 0 ? 1 : 2;
   float2* part = reinterpret_cast<float2*>(ws + pl.off_part);
-  float* lse = reinterpret_cast<float*>(ws + pl.off_lse);
   float* col = reinterpret_cast<float*>(ws + pl.off_col);
   const uint4* kk = static_cast<const uint4*>(k);
   const uint4* vv = static_cast<const uint4*>(v);
@@ -994,7 +987,7 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
                                 : score_mfma_kernel<D, W, kFused, 2, P>;
     hipLaunchKernelGGL(fused, dim3(grid), dim3(64 * W), keybuf > dec_lds ? keybuf : dec_lds,
                        stream, kk, vv, qq, N, K, R, pl.n_slab, 1, pl.split_keys, c, pool, kind,
-                       lse_win, part, lse, col, vrange, attn, ord, qd, dec.G, dec.out, dl_stride,
+                       lse_win, part, 0, col, vrange, attn, ord, qd, dec.G, dec.out, dl_stride,
                        status);
     return;
   }
@@ -1007,12 +1000,10 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
                               : score_mfma_kernel<D, W, kPass1, 2, P>;
   hipLaunchKernelGGL(pass1, dim3((unsigned)(n_inst * pl.n_slab * n1)), dim3(64 * W), dec_lds,
                      stream, kk, vv, qq, N, K, R, pl.n_slab, n1, keys1, c, pool, kind, lse_win,
-                     part, lse, col, vrange, attn, nullptr, qd, dec.G, dec.out, dl_stride, nullptr);
-  hipLaunchKernelGGL(score_lse_kernel, dim3((R + kSBlock - 1) / kSBlock, n_inst), dim3(kSBlock), 0,
-                     stream, part, R, n1, lse_win, lse, status);
+                     part, 0, col, vrange, attn, nullptr, qd, dec.G, dec.out, dl_stride, nullptr);
   hipLaunchKernelGGL((score_mfma_kernel<D, W, kPass2, 0, P>), dim3(grid), dim3(64 * W), keybuf, stream,
                      kk, vv, qq, N, K, R, pl.n_slab, pl.n_chunk1, pl.split_keys, c, pool, kind,
-                     nullptr, part, lse, col, vrange, attn, nullptr, nullptr, 0, nullptr, 0, status);
+                     lse_win, part, n1, col, vrange, attn, nullptr, nullptr, 0, nullptr, 0, status);
 }
 
 template <int D>
@@ -1037,6 +1028,41 @@ void launch_mfma(const void* k, const void* v, const void* q, int n_inst, int N,
 
 }  // namespace
 
+namespace {
+
+// ranges that n_split equal ones of whole chunks come down to
+int split_ranges(int N, int n_split) {
+  const int keys = ((N + n_split - 1) / n_split + kChunk - 1) / kChunk * kChunk;
+  return (N + keys - 1) / keys;
+}
+
+// Ranges per (instance, slab) for `base` of them, few enough that the chip is
+// not full.  A pass takes rounds of 256 CUs (two workgroups of four waves to a
+// CU) x (chunks of a range + what a workgroup costs besides: its rows' load,
+// the ring's fill, the reductions, about 5 chunks of eight waves or 8 of four),
+// and each range one more partial per row to merge.  64 instances of 132 chunks:
+// 4 ranges in one round 96 us, against 15 in 3.75 rounds 150 us.
+constexpr int kMostMerged = 48;   // more ranges cost more to merge than they save
+int pick_split(long long base, int chunks, int least, int most, int waves) {
+  const long long slots = waves == 8 ? 256 : 512;
+  const double own = waves == 8 ? 5 : 8;
+  const int last = least > kMostMerged ? least : (most < kMostMerged ? most : kMostMerged);
+  int best_n = least;
+  double best = 0;
+  for (int n = least; n <= last; ++n) {
+    const int per = (chunks + n - 1) / n;
+    const long long rounds = (base * ((chunks + per - 1) / per) + slots - 1) / slots;
+    const double t = (double)rounds * (per + own) + 0.05 * n;
+    if (n == least || t < best) {
+      best = t;
+      best_n = n;
+    }
+  }
+  return best_n;
+}
+
+}  // namespace
+
 ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
   ScorePlan pl{};
   const int N = K + B;
@@ -1050,20 +1076,21 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
     pl.rows_per_slab = 64 * pl.waves;
     pl.n_slab = (R + pl.rows_per_slab - 1) / pl.rows_per_slab;
     // one slot range per (instance, slab) when that alone gives >= 512 workgroups
-    // and the range's column sums fit in LDS; otherwise split the slots so that
-    // about 1024 workgroups run
+    // and the range's column sums fit in LDS; otherwise the slots are split.  The
+    // workspace has room for as many ranges as give about 1024 workgroups.
     const long long base = (long long)n_inst * pl.n_slab;
+    const int chunks = (N + kChunk - 1) / kChunk;
     int n_split = (N + kMaxSplitKeys - 1) / kMaxSplitKeys;
+    int most = n_split;
     if (base < 512) {
       const long long want = (1024 + base - 1) / base;
-      const int max_split = (N + kChunk - 1) / kChunk;
-      const int more = (int)(want < max_split ? want : max_split);
-      n_split = more > n_split ? more : n_split;
+      const int more = (int)(want < chunks ? want : chunks);
+      most = more > n_split ? more : n_split;
     }
-    const int per = (N + n_split - 1) / n_split;
-    pl.split_keys = (per + kChunk - 1) / kChunk * kChunk;
-    pl.n_chunk1 = (N + pl.split_keys - 1) / pl.split_keys;
-    pl.n_chunk2 = pl.n_chunk1;
+    pl.n_chunk2 = split_ranges(N, most);
+    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, chunks, n_split, pl.n_chunk2, pl.waves))
+                             : pl.n_chunk2;
+    pl.split_keys = ((N + pl.n_chunk1 - 1) / pl.n_chunk1 + kChunk - 1) / kChunk * kChunk;
   } else {
     pl.waves = 0;
     pl.split_keys = 0;
@@ -1078,14 +1105,13 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
     return pl;
   }
   pl.off_part = 0;
-  // the fused MFMA kernel needs no row partials, and pools by itself when one
-  // workgroup holds the instance's every row
-  const bool fused = pl.mfma && pl.n_chunk1 == 1;
-  pl.pool_in_kernel = fused && pl.n_slab == 1;
-  pl.off_lse = fused ? 0 : align256((size_t)n_inst * pl.n_chunk1 * R * sizeof(float2));
-  const size_t lse_bytes = fused ? 0 : align256((size_t)n_inst * R * sizeof(float));
-  pl.off_col = pl.off_lse + lse_bytes;
-  pl.bytes = pl.pool_in_kernel ? 0 : pl.off_col + align256((size_t)n_inst * pl.n_slab * K * sizeof(float));
+  // one workgroup that holds the instance's every row and slot pools by itself
+  pl.pool_in_kernel = pl.n_chunk1 == 1 && pl.n_slab == 1;
+  // row partials only where the slots may be split
+  pl.off_col = pl.n_chunk2 == 1 ? 0 : align256((size_t)n_inst * pl.n_chunk2 * R * sizeof(float2)) +
+                                          align256((size_t)n_inst * R * sizeof(float));
+  pl.bytes = pl.n_chunk2 == 1 && pl.n_slab == 1
+                 ? 0 : pl.off_col + align256((size_t)n_inst * pl.n_slab * K * sizeof(float));
   (void)d;
   return pl;
 }

@@ -313,7 +313,6 @@ void score_f32_split(int n_inst, int N, int K, int R, size_t part_bytes, ScorePl
     }
   }
   pl.off_part = 0;
-  pl.off_lse = 0;
   pl.off_col = ((size_t)n_inst * pl.n_chunk1 * R * sizeof(float2) + 255) & ~(size_t)255;
   const size_t spare = part_bytes - pl.off_col;
   const long long kt2 = (long long)n_inst * ((K + kTile - 1) / kTile);

@@ -172,14 +172,14 @@ __device__ __forceinline__ uint32_t xcd_logical_block(uint32_t hw_block, uint32_
 // ---------------------------------------------------------------------------
 struct ScorePlan {
   int n_chunk1;     // slot ranges per instance of the row-statistics pass
-  int n_chunk2;     // bf16: of the probability pass; fp32: 32-key tiles (the grids' bound)
+  int n_chunk2;     // the most there can be: what the workspace has room for
   int n_slab;       // query-row slabs (partial column sums per slab)
   int rows_per_slab;
   int waves;        // bf16: waves per workgroup (64 query rows each)
   int split_keys;   // bf16: slots per range (multiple of 32)
   bool mfma;        // bf16
   bool pool_in_kernel;  // bf16, one range and one slab per instance: no pool launch
-  size_t off_part, off_lse, off_col, bytes;
+  size_t off_part, off_col, bytes;
 };
 ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w);
 // lse_win (nullable): [n_inst][G*w] natural-log LSE of each window row over

@@ -1,0 +1,68 @@
+"""The window score where an instance's slots, runs or row slabs are split over
+workgroups: every way the plan splits a call, against the definition in float64.
+
+Each score is a mean of softmax terms computed in fp32 (exp2 within 1 ulp, a sum
+of at most 2^15 non-negative terms in fixed trees, an fp32 logarithm of the
+normaliser), so 2e-5 of the largest score bounds the difference with room."""
+import math
+
+import pytest
+import torch
+
+from paper_2606_03928_amd import vase
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(autouse=True)
+def _lib(gpu_lib):
+    yield
+    torch.cuda.synchronize()
+
+
+def _reference(k, v, q, K, pool):
+    n, G, w, d = q.shape
+    s = torch.bmm(q.double().reshape(n, G * w, d), k.double().transpose(1, 2).contiguous())
+    s = s / math.sqrt(d)
+    p = torch.softmax(s, -1)[:, :, :K].mean(1)
+    p = torch.nn.functional.pad(p, (pool // 2, pool // 2)).unfold(1, pool, 1).sum(-1) / pool
+    lse = torch.logsumexp(s[:, :, :K], -1).view(n, G, w).float()
+    vd = v[:, :K].double()
+    return p, lse, (vd.amax(-1) - vd.amin(-1)).float()
+
+
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("dtype,n,K,B,d,G,w", [
+    # bf16: one range although the chip is not full, ranges of one chunk, ranges
+    # that do not divide, partials merged four at a time with 1 to 3 left over
+    (BF, 400, 96, 8, 64, 2, 16), (BF, 1, 33, 1, 128, 1, 1), (BF, 3, 2000, 77, 128, 4, 65),
+    (BF, 8, 545, 32, 64, 8, 33), (BF, 64, 700, 65, 128, 5, 130),
+    # fp32: one row, a window one row past a tile and past the rows whose
+    # normalisers fit at once, row slabs, runs that do not divide, 24 runs
+    (F32, 1, 1, 1, 64, 1, 1), (F32, 2, 31, 2, 128, 3, 11), (F32, 1, 200, 9, 64, 5, 205),
+    (F32, 5, 1000, 33, 128, 8, 36), (F32, 40, 127, 64, 64, 1, 97), (F32, 1, 5000, 100, 128, 2, 20),
+])
+def test_split_scores(dtype, n, K, B, d, G, w):
+    g = torch.Generator(device="cpu")
+    g.manual_seed(n * K + B + G * w)
+    k, v = (torch.randn((n, K + B, d), generator=g).to(dtype).to(DEV) for _ in range(2))
+    q = torch.randn((n, G, w, d), generator=g).to(dtype).to(DEV)
+    pool = 3 if K > 3 else 1
+    want, lse, want_vr = _reference(k, v, q, K, pool)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    for lse_win in (None, lse):
+        attn, vr = vase.score(k, v, q, K, B, pool, lse_win=lse_win, status=status)
+        err = (attn.double() - want).abs().amax(1) / want.amax(1)
+        assert err.max().item() < 2e-5
+        # the Range of bf16 rows is exact in fp32, that of fp32 rows one rounding
+        assert ((vr - want_vr).abs() <= (0 if dtype == BF else 2 ** -23) * want_vr).all()
+    assert status.item() == 0
+    # a row fault is seen by whichever workgroup merges the row, a value fault
+    # by the one that reads it
+    q[n - 1, G - 1, w - 1, d - 1] = float("nan")
+    v[n - 1, K - 1, 0] = float("inf")
+    vase.score(k, v, q, K, B, pool, status=status)
+    assert status.item() == vase.STATUS_ROW_NORM | vase.STATUS_VALUE_ROW
