@@ -243,11 +243,12 @@ namespace {
 
 int decode_common(const void* k_cache, const void* v_cache, const void* q, int dtype, int n_inst,
                   int K, int B, int d, int G, int n_valid, int n_persist, void* out, float* lse,
-                  int lse_ld, void* ws, size_t ws_bytes, hipStream_t s) {
+                  int lse_ld, void* ws, size_t ws_bytes, hipStream_t s,
+                  const vase::DecodeToken& tok = vase::DecodeToken()) {
   const vase::DecodePlan plan = vase::decode_plan(dtype, n_inst, K, B, d, G, n_valid, n_persist);
   if (plan.bytes > 0 && (!ws || ws_bytes < plan.bytes || !aligned16(ws))) return VASE_ERR_WORKSPACE;
   return hip_status(vase::launch_decode(k_cache, v_cache, q, dtype, n_inst, K, B, d, G, n_valid,
-                                        n_persist, out, lse, lse_ld, ws, plan, s));
+                                        n_persist, out, lse, lse_ld, ws, plan, s, tok));
 }
 
 }  // namespace
@@ -288,14 +289,9 @@ int vase_decode_step(void* k_cache, void* v_cache, const void* k_new, const void
   if (!aligned16(k_cache) || !aligned16(v_cache) || !aligned16(k_new) || !aligned16(v_new) ||
       !aligned16(q) || !aligned16(q_win) || !aligned16(lse_win) || !aligned16(out))
     return VASE_ERR_INVALID_ARG;
-  const vase::DecodePlan plan = vase::decode_plan(dtype, n_inst, K, B, d, G, K + pos + 1, K);
-  if (plan.bytes > 0 && (!ws || ws_bytes < plan.bytes || !aligned16(ws))) return VASE_ERR_WORKSPACE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = vase::launch_decode_append(k_cache, v_cache, k_new, v_new, q, q_win, dtype,
-                                                  n_inst, K, B, d, G, w, pos, s);
-  if (e != hipSuccess) return VASE_ERR_HIP;
   return decode_common(k_cache, v_cache, q, dtype, n_inst, K, B, d, G, K + pos + 1, K, out,
-                       lse_win + pos % w, w, ws, ws_bytes, s);
+                       lse_win + pos % w, w, ws, ws_bytes, static_cast<hipStream_t>(stream),
+                       vase::DecodeToken{k_new, v_new, q_win, w, pos});
 }
 
 int vase_decode_step_noalloc(void* k_cache, void* v_cache, const void* k_new, const void* v_new,
@@ -315,12 +311,9 @@ int vase_decode_step_noalloc(void* k_cache, void* v_cache, const void* k_new, co
   if (plan.bytes > VASE_DECODE_SCRATCH_BYTES) return VASE_ERR_WORKSPACE;
   void* ws = nullptr;
   if (plan.bytes > 0 && vase::decode_scratch(&ws) != hipSuccess) return VASE_ERR_HIP;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t e = vase::launch_decode_append(k_cache, v_cache, k_new, v_new, q, q_win, dtype,
-                                                  n_inst, K, B, d, G, w, pos, s);
-  if (e != hipSuccess) return VASE_ERR_HIP;
   return decode_common(k_cache, v_cache, q, dtype, n_inst, K, B, d, G, K + pos + 1, K, out,
-                       lse_win + pos % w, w, ws, plan.bytes, s);
+                       lse_win + pos % w, w, ws, plan.bytes, static_cast<hipStream_t>(stream),
+                       vase::DecodeToken{k_new, v_new, q_win, w, pos});
 }
 
 int vase_compact_decode_ex(void* k_cache, void* v_cache, int dtype, int n_inst, int K, int B,

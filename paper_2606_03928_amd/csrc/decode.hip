@@ -50,12 +50,36 @@ __device__ __forceinline__ float lse_nat(float m, float l) {
   return (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
+// A decode step's new token: cache row n_valid - 1 (`slot`) takes k_new and v_new,
+// and q_win[inst][g][ring] takes q[inst][g] (byte copies).  The workgroup whose
+// rows include the slot writes them and takes the row itself from k_new and
+// v_new; no other workgroup reads it.  As a launch of its own ahead of the
+// attention this cost 2.5 us and a gap in a step of 16 (8 instances, 2089 rows).
+struct DecAppend {
+  const uint4 *k_new, *v_new;   // [n_inst][row]; null: no append
+  uint4* q_win;                 // [n_inst][G][w][row]
+  int w, ring;
+};
+
+template <int BLOCK>
+__device__ __forceinline__ void append_rows(const DecAppend& ap, uint4* kb, uint4* vb, const uint4* q,
+                                            int inst, int slot, int G, int row_u4) {
+  for (int t = threadIdx.x; t < (2 + G) * row_u4; t += BLOCK) {
+    const int r = t / row_u4, c = t % row_u4;
+    if (r == 0) kb[(size_t)slot * row_u4 + c] = ap.k_new[(size_t)inst * row_u4 + c];
+    else if (r == 1) vb[(size_t)slot * row_u4 + c] = ap.v_new[(size_t)inst * row_u4 + c];
+    else
+      ap.q_win[(((size_t)inst * G + r - 2) * ap.w + ap.ring) * row_u4 + c] =
+          q[((size_t)inst * G + r - 2) * row_u4 + c];
+  }
+}
+
 template <typename T, int D, int G, int UNROLL>
 __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
-    const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ q, int N,
-    int n_valid, int n_persist, int s1, int rows_per_split, int n_split, float scale_log2,
-    float* __restrict__ part /* [n_inst][n_split][G][kPartHead + D] */, T* __restrict__ out,
-    float* __restrict__ lse, int lse_ld) {
+    T* k, T* v, const T* q, int N, int n_valid, int n_persist, int s1, int rows_per_split,
+    int n_split, float scale_log2,
+    float* __restrict__ part /* [n_inst][n_split][G][kPartHead + D] */, T* out,
+    float* __restrict__ lse, int lse_ld, DecAppend ap) {
   constexpr int VEC = Vec16<T>::n;          // elements per lane
   constexpr int LPR = D / VEC;              // lanes per row
   constexpr int RPW = kWave / LPR;          // rows per wave per load
@@ -69,8 +93,12 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
   const int r_lo = split < s1 ? split * rows_per_split : n_persist + (split - s1) * rows_per_split;
   const int r_hi = min(split < s1 ? n_persist : n_valid, r_lo + rows_per_split);
 
-  const uint4* kb = reinterpret_cast<const uint4*>(k + (size_t)inst * N * D);
-  const uint4* vb = reinterpret_cast<const uint4*>(v + (size_t)inst * N * D);
+  uint4* kb = reinterpret_cast<uint4*>(k + (size_t)inst * N * D);
+  uint4* vb = reinterpret_cast<uint4*>(v + (size_t)inst * N * D);
+  // the appended row's slot: past every row when there is none
+  const int slot = ap.k_new ? n_valid - 1 : n_valid;
+  // its k_new and v_new as offsets from the cache rows
+  const ptrdiff_t kn = ap.k_new + (size_t)inst * LPR - kb, vn = ap.v_new + (size_t)inst * LPR - vb;
   float qf[G][VEC];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -96,8 +124,8 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
       const int r = r0 + u * RPB + rg;
       ok[u] = r < r_hi;
       const int rr = ok[u] ? r : r_lo;
-      kw[u] = kb[(size_t)rr * LPR + seg];
-      vw[u] = vb[(size_t)rr * LPR + seg];
+      kw[u] = kb[(rr == slot ? kn : (ptrdiff_t)rr * LPR) + seg];
+      vw[u] = vb[(rr == slot ? vn : (ptrdiff_t)rr * LPR) + seg];
     }
     float s[UNROLL][G];
 #pragma unroll
@@ -138,6 +166,8 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
     }
   }
 
+  if (slot < n_valid && split == n_split - 1)
+    append_rows<kDecBlock>(ap, kb, vb, reinterpret_cast<const uint4*>(q), inst, slot, G, LPR);
   // merge the RPW row groups of the wave (lane bits above log2(LPR)), fixed order
 #pragma unroll
   for (int off = LPR; off < kWave; off <<= 1) {
@@ -214,9 +244,9 @@ typedef float df32x4 __attribute__((ext_vector_type(4)));
 
 template <int D, int G>
 __global__ __launch_bounds__(kDecBlock) void decode_mfma_kernel(
-    const uint4* __restrict__ k, const uint4* __restrict__ v, const uint4* __restrict__ q, int N,
-    int n_valid, int n_persist, int s1, int rows_per_split, int n_split, float scale_log2,
-    float* __restrict__ part, bf16_t* __restrict__ out, float* __restrict__ lse, int lse_ld) {
+    uint4* k, uint4* v, const uint4* q, int N, int n_valid, int n_persist, int s1,
+    int rows_per_split, int n_split, float scale_log2, float* __restrict__ part, bf16_t* out,
+    float* __restrict__ lse, int lse_ld, DecAppend ap) {
   constexpr int KS = D / 32;           // MFMA depth steps
   constexpr int PPR = D / 8;           // 16-byte pieces per row
   constexpr int LG = kWave / PPR;      // lane groups of the P.V layout
@@ -229,15 +259,20 @@ __global__ __launch_bounds__(kDecBlock) void decode_mfma_kernel(
   __shared__ float s_mlp[kDecWaves][G][2];   // the persistent rows' state
 
   const int split = blockIdx.x, inst = blockIdx.y;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // uniform per wave
   // when n_split = s1, split s1 - 1 also covers [n_persist, n_valid)
   const int r_lo = split < s1 ? split * rows_per_split : n_persist + (split - s1) * rows_per_split;
   const int r_hi = split == n_split - 1 ? n_valid
                                         : min(split < s1 ? n_persist : n_valid, r_lo + rows_per_split);
-  const uint4* kb = k + (size_t)inst * N * PPR;
-  const uint4* vb = v + (size_t)inst * N * PPR;
+  uint4* kb = k + (size_t)inst * N * PPR;
+  uint4* vb = v + (size_t)inst * N * PPR;
   const int hm = lane % 16, hq = lane / 16;    // MFMA layout
   const int pp = lane % PPR, lg = lane / PPR;  // P.V layout
+  // the appended row's slot: past every row when there is none
+  const int slot = ap.k_new ? n_valid - 1 : n_valid;
+  // its k_new and v_new as offsets from the cache rows
+  const ptrdiff_t kn = ap.k_new + (size_t)inst * PPR - kb, vn = ap.v_new + (size_t)inst * PPR - vb;
 
   dbf16x8 bq[KS];
 #pragma unroll
@@ -267,10 +302,20 @@ __global__ __launch_bounds__(kDecBlock) void decode_mfma_kernel(
     }
     uint4 ka[KS], vv[RPL];
     const int rk = min(row0 + hm, r_hi - 1);
+    ptrdiff_t ko = (ptrdiff_t)rk * PPR, vo[RPL];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ka[ks] = kb[(size_t)rk * PPR + 4 * ks + hq];
+    for (int i = 0; i < RPL; ++i) vo[i] = (ptrdiff_t)min(row0 + lg + LG * i, r_hi - 1) * PPR;
+    if (row0 + 16 > slot) {                    // the tile with the appended row
+      if (rk == slot) ko = kn;
 #pragma unroll
-    for (int i = 0; i < RPL; ++i) vv[i] = vb[(size_t)min(row0 + lg + LG * i, r_hi - 1) * PPR + pp];
+      for (int i = 0; i < RPL; ++i)
+        if (min(row0 + lg + LG * i, r_hi - 1) == slot) vo[i] = vn;
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ka[ks] = kb[ko + 4 * ks + hq];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) vv[i] = vb[vo[i] + pp];
+    __builtin_amdgcn_sched_barrier(0);         // every load before the first MFMA waits
     df32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
@@ -317,6 +362,8 @@ __global__ __launch_bounds__(kDecBlock) void decode_mfma_kernel(
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // reads done before the next tile's writes
   }
+  if (slot < n_valid && split == n_split - 1)
+    append_rows<kDecBlock>(ap, kb, vb, q, inst, slot, G, PPR);
   if (p_open) {
     m_p = m_run;
     l_p = l_run;
@@ -382,64 +429,109 @@ __global__ __launch_bounds__(kDecBlock) void decode_mfma_kernel(
   }
 }
 
-template <typename T, int D>
+// One thread per (instance, head, dim): the splits' partials merged in split
+// order, U in flight; with ALL, U >= n_split and everything is loaded at once.
+// The call is a chain of memory latencies and otherwise bound by its loads: with
+// one workgroup per instance and one partial in flight it took 6.4 us for 8
+// instances of 8 splits (2.8 now) and 17 us for 64 of 16.
+template <typename T, int D, int U, bool ALL>
 __global__ __launch_bounds__(kDecBlock) void decode_combine_kernel(
-    const float* __restrict__ part, int n_split, int s1, int G, T* __restrict__ out,
+    const float* __restrict__ part, int n_split, int s1, int n_head, int G, T* __restrict__ out,
     float* __restrict__ lse, int lse_ld) {
-  const int inst = blockIdx.x;
-  for (int t = threadIdx.x; t < G * D; t += kDecBlock) {
-    const int g = t / D, dd = t % D;
-    const float* p0 = part + ((size_t)inst * n_split * G + g) * (kPartHead + D);
-    const size_t stride = (size_t)G * (kPartHead + D);
-    float mn = p0[0];
-    for (int s = 1; s < n_split; ++s) mn = fmaxf(mn, p0[s * stride]);
-    float lt = 0.f, ot = 0.f;
-    for (int s = 0; s < n_split; ++s) {
-      const float a = __builtin_amdgcn_exp2f(p0[s * stride] - mn);
-      lt += p0[s * stride + 1] * a;
-      ot += p0[s * stride + kPartHead + dd] * a;
+  constexpr int kPer = kDecBlock / D;   // heads per workgroup
+  const int head = blockIdx.x * kPer + threadIdx.x / D;   // inst * G + g
+  const int dd = threadIdx.x % D;
+  if (head >= n_head) return;
+  const int inst = head / G, g = head % G;
+  const float* p0 = part + ((size_t)inst * n_split * G + g) * (kPartHead + D);
+  const size_t stride = (size_t)G * (kPartHead + D);
+  // a partial's (m, l, m_p, l_p) and output; the persistent state counts in the
+  // splits that start below n_persist
+  float4 h[U];
+  float o[U];
+  auto load = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float* p = p0 + (size_t)min(s + u, n_split - 1) * stride;
+      h[u] = *reinterpret_cast<const float4*>(p);
+      o[u] = p[kPartHead + dd];
     }
-    store_out<T>(out + ((size_t)inst * G + g) * D + dd, ot / lt);
-    if (lse && dd == 0) {
-      // the persistent parts of the splits that start below n_persist, merged
-      // in the same order
-      float mp = p0[2];
-      for (int s = 1; s < s1; ++s) mp = fmaxf(mp, p0[s * stride + 2]);
-      float lp = 0.f;
-      for (int s = 0; s < s1; ++s) lp += p0[s * stride + 3] * __builtin_amdgcn_exp2f(p0[s * stride + 2] - mp);
-      lse[((size_t)inst * G + g) * lse_ld] = lse_nat(mp, lp);
+  };
+  float mn = -INFINITY, mp = -INFINITY;
+  auto maxima = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mn = fmaxf(mn, h[u].x);
+      mp = s + u < s1 ? fmaxf(mp, h[u].z) : mp;
+    }
+  };
+  float lt = 0.f, ot = 0.f, lp = 0.f;
+  auto sums = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float a = __builtin_amdgcn_exp2f(h[u].x - mn);
+      lt = s + u < n_split ? lt + h[u].y * a : lt;
+      ot = s + u < n_split ? ot + o[u] * a : ot;
+      lp = s + u < s1 ? lp + h[u].w * __builtin_amdgcn_exp2f(h[u].z - mp) : lp;
+    }
+  };
+  if constexpr (ALL) {
+    load(0);
+    maxima(0);
+    sums(0);
+  } else {
+    for (int s = 0; s < n_split; s += U) {
+      load(s);
+      maxima(s);
+    }
+    for (int s = 0; s < n_split; s += U) {
+      load(s);
+      sums(s);
     }
   }
+  store_out<T>(out + (size_t)head * D + dd, ot / lt);
+  if (lse && dd == 0) lse[(size_t)head * lse_ld] = lse_nat(mp, lp);
 }
 
 struct DecodeArgs {
-  const void *k, *v, *q;
+  void *k, *v;
+  const void* q;
   int n_inst, N, n_valid, n_persist;
   void* out;
   float* lse;
   int lse_ld;
+  DecAppend ap;
 };
+
+template <typename T, int D>
+void launch_combine(const float* part, int n_split, int s1, int n_inst, int G, void* out, float* lse,
+                    int lse_ld, hipStream_t stream) {
+  constexpr int kPer = kDecBlock / D;
+  auto kernel = n_split <= 2   ? decode_combine_kernel<T, D, 2, true>
+                : n_split <= 8 ? decode_combine_kernel<T, D, 8, true>
+                               : decode_combine_kernel<T, D, 8, false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((n_inst * G + kPer - 1) / kPer)), dim3(kDecBlock), 0,
+                     stream, part, n_split, s1, n_inst * G, G, static_cast<T*>(out), lse, lse_ld);
+}
 
 template <typename T, int D, int G>
 hipError_t launch_g(const DecodeArgs& a, float* ws, const DecodePlan& pl, hipStream_t stream) {
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   if constexpr (std::is_same<T, bf16_t>::value) {
     hipLaunchKernelGGL((decode_mfma_kernel<D, G>), dim3(pl.n_split, a.n_inst), dim3(kDecBlock), 0,
-                       stream, static_cast<const uint4*>(a.k), static_cast<const uint4*>(a.v),
+                       stream, static_cast<uint4*>(a.k), static_cast<uint4*>(a.v),
                        static_cast<const uint4*>(a.q), a.N, a.n_valid, a.n_persist, pl.s1,
                        pl.rows_per_split, pl.n_split, scale_log2, ws, static_cast<T*>(a.out),
-                       a.lse, a.lse_ld);
+                       a.lse, a.lse_ld, a.ap);
   } else {
     hipLaunchKernelGGL((decode_split_kernel<T, D, G, 4>), dim3(pl.n_split, a.n_inst),
-                       dim3(kDecBlock), 0, stream, static_cast<const T*>(a.k),
-                       static_cast<const T*>(a.v), static_cast<const T*>(a.q), a.N, a.n_valid,
-                       a.n_persist, pl.s1, pl.rows_per_split, pl.n_split, scale_log2, ws,
-                       static_cast<T*>(a.out), a.lse, a.lse_ld);
+                       dim3(kDecBlock), 0, stream, static_cast<T*>(a.k), static_cast<T*>(a.v),
+                       static_cast<const T*>(a.q), a.N, a.n_valid, a.n_persist, pl.s1,
+                       pl.rows_per_split, pl.n_split, scale_log2, ws, static_cast<T*>(a.out),
+                       a.lse, a.lse_ld, a.ap);
   }
-  if (pl.n_split > 1) {
-    hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(a.n_inst), dim3(kDecBlock), 0, stream,
-                       ws, pl.n_split, pl.s1, G, static_cast<T*>(a.out), a.lse, a.lse_ld);
-  }
+  if (pl.n_split > 1)
+    launch_combine<T, D>(ws, pl.n_split, pl.s1, a.n_inst, G, a.out, a.lse, a.lse_ld, stream);
   return hipGetLastError();
 }
 
@@ -458,27 +550,6 @@ hipError_t launch_d(const DecodeArgs& a, int G, float* ws, const DecodePlan& pl,
   }
 }
 
-// Append one token and cache its query: rows K + pos of k and v take k_new and
-// v_new, and q_win[inst][g][pos % w] takes q[inst][g] (byte copies).
-__global__ __launch_bounds__(256) void decode_append_kernel(
-    uint4* __restrict__ k, uint4* __restrict__ v, const uint4* __restrict__ k_new,
-    const uint4* __restrict__ v_new, const uint4* __restrict__ q, uint4* __restrict__ q_win,
-    int N, int slot, int G, int w, int ring, int row_u4) {
-  const int inst = blockIdx.x;
-  for (int t = threadIdx.x; t < (2 + G) * row_u4; t += 256) {
-    const int r = t / row_u4, c = t % row_u4;
-    if (r == 0) k[((size_t)inst * N + slot) * row_u4 + c] = k_new[(size_t)inst * row_u4 + c];
-    else if (r == 1) v[((size_t)inst * N + slot) * row_u4 + c] = v_new[(size_t)inst * row_u4 + c];
-    else {
-      const int g = r - 2;
-      q_win[(((size_t)inst * G + g) * w + ring) * row_u4 + c] = q[((size_t)inst * G + g) * row_u4 + c];
-    }
-  }
-}
-
-}  // namespace
-
-namespace {
 // key splits for n_valid rows: at least 4096 workgroups over the chip (one
 // workgroup per instance leaves the last of ~2.25 dispatch waves a quarter
 // full at 2304 instances; two splits cut a step from 1.10 to 0.87 ms there),
@@ -522,8 +593,12 @@ size_t decode_ws_bytes_max(int dtype, int n_inst, int K, int B, int d, int G) {
 hipError_t launch_decode(const void* k, const void* v, const void* q, int dtype, int n_inst,
                          int K, int B, int d, int G, int n_valid, int n_persist, void* out,
                          float* lse, int lse_ld, void* ws, const DecodePlan& plan,
-                         hipStream_t stream) {
-  const DecodeArgs a{k, v, q, n_inst, K + B, n_valid, n_persist, out, lse, lse_ld};
+                         hipStream_t stream, const DecodeToken& tok) {
+  // without a token to append the kernels write no cache row
+  const DecodeArgs a{const_cast<void*>(k), const_cast<void*>(v), q, n_inst, K + B, n_valid,
+                     n_persist, out, lse, lse_ld,
+                     DecAppend{static_cast<const uint4*>(tok.k_new), static_cast<const uint4*>(tok.v_new),
+                               static_cast<uint4*>(tok.q_win), tok.w, tok.w ? tok.pos % tok.w : 0}};
   float* w = static_cast<float*>(ws);
   if (dtype == VASE_BF16) {
     if (d == 128) return launch_d<bf16_t, 128>(a, G, w, plan, stream);
@@ -551,18 +626,6 @@ hipError_t decode_scratch(void** ptr) {
   }
   *ptr = g_scratch_ptr[dev];
   return hipSuccess;
-}
-
-hipError_t launch_decode_append(void* k, void* v, const void* k_new, const void* v_new,
-                                const void* q, void* q_win, int dtype, int n_inst, int K, int B,
-                                int d, int G, int w, int pos, hipStream_t stream) {
-  const int row_u4 = d * (dtype == VASE_BF16 ? 2 : 4) / 16;
-  hipLaunchKernelGGL(decode_append_kernel, dim3(n_inst), dim3(256), 0, stream,
-                     static_cast<uint4*>(k), static_cast<uint4*>(v),
-                     static_cast<const uint4*>(k_new), static_cast<const uint4*>(v_new),
-                     static_cast<const uint4*>(q), static_cast<uint4*>(q_win), K + B, K + pos, G, w,
-                     pos % w, row_u4);
-  return hipGetLastError();
 }
 
 }  // namespace vase

@@ -259,13 +259,17 @@ constexpr size_t kDecodeScratchBytes = (size_t)64 << 20;
 hipError_t decode_scratch(void** ptr);
 // lse (nullable): natural-log LSE over slots [0, n_persist) for each query head,
 // written to lse[(inst * G + g) * lse_ld]
+// tok (k_new set): one token is appended by the same launch: cache row
+// n_valid - 1 takes k_new and v_new, q_win[inst][g][pos % w] takes q[inst][g]
+struct DecodeToken {
+  const void *k_new = nullptr, *v_new = nullptr;   // [n_inst][d]
+  void* q_win = nullptr;                           // [n_inst][G][w][d]
+  int w = 0, pos = 0;
+};
 hipError_t launch_decode(const void* k, const void* v, const void* q, int dtype, int n_inst,
                          int K, int B, int d, int G, int n_valid, int n_persist, void* out,
                          float* lse, int lse_ld, void* ws, const DecodePlan& plan,
-                         hipStream_t stream);
-hipError_t launch_decode_append(void* k, void* v, const void* k_new, const void* v_new,
-                                const void* q, void* q_win, int dtype, int n_inst, int K, int B,
-                                int d, int G, int w, int pos, hipStream_t stream);
+                         hipStream_t stream, const DecodeToken& tok = DecodeToken());
 
 // The cache under an order map (ord[inst][t] = slot of temporal rank t < K).
 // attn_out[t] = P-wide box filter over temporal ranks of attn_phys[ord[.]];
