@@ -341,8 +341,7 @@ int vase_decode_step_noalloc(void* k_cache, void* v_cache, const void* k_new, co
  * n_valid = K (Sec. 2: after an eviction round the decoder continues over the
  * restored K-slot cache; Eq. 1).  The results are those of the two calls in
  * sequence (the same cache bytes; the same attention output up to fp32
- * summation order).  When each instance fits one workgroup, the cache is read
- * once for both steps; otherwise the two steps run one after the other.
+ * summation order).  The cache is read once for both steps.
  *
  *  k_cache, v_cache  in/out [n_inst][N][d] device, dtype
  *  src               in     [n_inst][K] device int32 survivor map (vase_select)

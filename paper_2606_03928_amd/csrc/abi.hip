@@ -28,19 +28,6 @@ int check_cache_shape(int n_inst, int K, int B, int d) {
 
 int hip_status(hipError_t e) { return e == hipSuccess ? VASE_OK : VASE_ERR_HIP; }
 
-// vase_compact_decode runs one fused kernel (no workspace) when each instance
-// fits one workgroup, else compaction then decode, which share the workspace
-bool compact_decode_fused(int dtype, int n_inst, int K, int B, int d) {
-  return vase::compact_plan(dtype, n_inst, K, B, d).n_part == 1 && K <= vase::kCompactDecodeMaxK;
-}
-
-size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
-  if (compact_decode_fused(dtype, n_inst, K, B, d)) return 0;
-  const size_t a = vase::compact_plan(dtype, n_inst, K, B, d).bytes;
-  const size_t b = vase::decode_plan(dtype, n_inst, K, B, d, G, K, K).bytes;
-  return a > b ? a : b;
-}
-
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // score under an order map: the score's own workspace, then room for two fp32
@@ -85,7 +72,7 @@ size_t vase_workspace_bytes(int op, int dtype, int n_inst, int K, int B, int d, 
       return vase::compact_plan(dtype, n_inst, K, B, d).bytes;
     case VASE_OP_COMPACT_DECODE:
       if (G < 1) return 0;
-      return compact_decode_bytes(dtype, n_inst, K, B, d, G);
+      return vase::compact_decode_bytes(dtype, n_inst, K, B, d, G);
     case VASE_OP_SCORE_MAP:
       if (G < 1 || w < 1) return 0;
       return score_map_bytes(dtype, n_inst, K, B, d, G, w);
@@ -330,23 +317,12 @@ int vase_compact_decode_ex(void* k_cache, void* v_cache, int dtype, int n_inst, 
   if (!aligned16(k_cache) || !aligned16(v_cache) || !aligned16(src) || !aligned16(q) ||
       !aligned16(out) || (vrange_out && !aligned16(vrange_out)))
     return VASE_ERR_INVALID_ARG;
-  const vase::CompactPlan cp = vase::compact_plan(dtype, n_inst, K, B, d);
-  const vase::DecodePlan dp = vase::decode_plan(dtype, n_inst, K, B, d, G, K, K);
-  const size_t need = compact_decode_bytes(dtype, n_inst, K, B, d, G);
+  const size_t need = vase::compact_decode_bytes(dtype, n_inst, K, B, d, G);
   if (need > 0 && (!ws || ws_bytes < need || !aligned16(ws))) return VASE_ERR_WORKSPACE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (compact_decode_fused(dtype, n_inst, K, B, d)) {
-    return hip_status(vase::launch_compact_decode(k_cache, v_cache, dtype, n_inst, K, B, d, src, q,
-                                                  G, out, value_kind, vrange_out, s));
-  }
-  // instances split over several workgroups (or very long): compaction, the
-  // compacted rows' value scores, then decode
-  hipError_t e = vase::launch_compact(k_cache, v_cache, dtype, n_inst, K, B, d, src, ws, cp, s);
-  if (e == hipSuccess && vrange_out)
-    e = vase::launch_value_rows(v_cache, dtype, n_inst, K + B, K, d, value_kind, vrange_out, s);
-  if (e != hipSuccess) return VASE_ERR_HIP;
-  return hip_status(vase::launch_decode(k_cache, v_cache, q, dtype, n_inst, K, B, d, G, K, K, out,
-                                        nullptr, 1, ws, dp, s));
+  const vase::CompactPlan plan = vase::compact_decode_plan(dtype, n_inst, K, B, d, G);
+  return hip_status(vase::launch_compact_decode(k_cache, v_cache, dtype, n_inst, K, B, d, src, q, G,
+                                                out, value_kind, vrange_out, ws, plan,
+                                                static_cast<hipStream_t>(stream)));
 }
 
 int vase_compact_decode(void* k_cache, void* v_cache, int dtype, int n_inst, int K, int B, int d,

@@ -14,7 +14,7 @@
 //     earlier store touches.
 //
 // Rows in the unmoved prefix (src[j] == j) are skipped; src[j] - j is
-// non-decreasing, so that prefix is found by binary search.
+// non-decreasing, so compact_move_kernel finds that prefix by binary search.
 #include "vase_internal.hpp"
 #include "vase.h"
 
@@ -116,43 +116,60 @@ __global__ __launch_bounds__(kCompBlock) void compact_move_kernel(
 
 // ---------------------------------------------------------------------------
 // Compaction fused with one decode-attention step (Eq. 1) over the compacted
-// cache.  One workgroup per instance reads every survivor row exactly once (the
-// unmoved prefix is read but not written), stores the rows that move, and
-// accumulates the G query heads' online softmax over the rows it holds in
-// registers, so the decode costs no extra pass over the cache.
+// cache: a workgroup takes one part [p T, (p+1) T) of an instance's destination
+// rows, reads every survivor row of it exactly once (rows in place are read but
+// not written), stores the rows that move, and accumulates the G query heads'
+// online softmax over the rows it holds in registers, so that the decode and
+// the value scores cost no further pass over the cache.  With one part per
+// instance it writes the outputs itself; else the partials (m, l, o) of the
+// parts go to the decode's combine, and rows from the next part's range are
+// read from their staged copies, as in compact_move_kernel.
 //
-// Rows go in chunks, in ascending order.  A chunk's stores wait until every
-// thread's loads of that chunk have completed (vmcnt, then a barrier): a row
-// may be read and overwritten within one chunk.  The loads of the next two
-// chunks are in flight meanwhile: they read rows src[j] >= j at or above the
-// next chunk's first row, which no store of this or an earlier chunk touches.  The survivor map sits in LDS, so no load waits for an index.
+// Bound by HBM: 2 rows read and up to 2 written per slot.  Rows go in chunks, in
+// ascending order.  A chunk's stores wait until every thread's loads of that
+// chunk have completed (vmcnt, then a barrier): a row may be read and
+// overwritten within one chunk.  The loads of the next two chunks are in flight
+// meanwhile: they read rows src[j] >= j at or above the next chunk's first row,
+// which no store of this or an earlier chunk touches.  The survivor map sits in
+// LDS (kMapRows of it at a time), so no load waits for an index; the three
+// register stages rotate by name, since a stage that is copied to another one
+// has to have arrived first.
+//
+// 64 instances of 4096 rows (d = 128, G = 4, bf16, 268 MB to move): 129 -> 58 us
+// against staging, moving, scoring and decoding in launches of their own, which
+// went over the cache three times; 576 instances 928 -> 565 us; 512 fp32
+// instances 1558 -> 880 us.
 // ---------------------------------------------------------------------------
+constexpr int kMapRows = 4096;
+
 template <typename T, int D, int G, bool CARRY>
 __global__ __launch_bounds__(kCompBlock) void compact_decode_kernel(
-    uint4* __restrict__ k, uint4* __restrict__ v, const int32_t* __restrict__ src, int K, int B,
-    const T* __restrict__ q, T* __restrict__ out, float scale_log2, int value_kind,
-    float* __restrict__ vrange) {
+    uint4* k, uint4* v, const int32_t* __restrict__ src, int K, int B, int rows_per_part,
+    int n_part, const uint4* __restrict__ stage, const T* __restrict__ q, T* __restrict__ out,
+    float* __restrict__ part, float scale_log2, int value_kind, float* __restrict__ vrange) {
   constexpr int VEC = Vec16<T>::n;            // elements per 16-byte piece
   constexpr int ROW_U4 = D / VEC;             // pieces (lanes) per row
   constexpr int kRowsPerPass = kCompBlock / ROW_U4;
   constexpr int kPasses = 2;
   constexpr int CHUNK = kRowsPerPass * kPasses;
   constexpr int kWaves = kCompBlock / kWave;
-  __shared__ int s_start;
+  static_assert(kMapRows % CHUNK == 0, "whole chunks per map segment");
   __shared__ float s_o[kWaves][G][D];
   __shared__ float s_ml[kWaves][G][2];
-  extern __shared__ int s_src[];              // [K] survivor map of this instance
-  const int inst = blockIdx.x;
+  __shared__ int s_src[kMapRows];
+  const int p = (int)(blockIdx.x % (unsigned)n_part), inst = (int)(blockIdx.x / (unsigned)n_part);
   const int N = K + B;
   const int32_t* s = src + (size_t)inst * K;
-  for (int i = threadIdx.x; i < K; i += kCompBlock) s_src[i] = clamp_slot(s[i], N);
-  __syncthreads();
-  if (threadIdx.x == 0) s_start = first_moved(s_src, 0, K);
+  const int j_lo = p * rows_per_part, j_hi = min(K, j_lo + rows_per_part);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int col = threadIdx.x % ROW_U4;
   const int row0 = threadIdx.x / ROW_U4;
   uint4* kb = k + (size_t)inst * N * ROW_U4;
   uint4* vb = v + (size_t)inst * N * ROW_U4;
+  // source rows at or above stage_lo come from the staging area
+  const bool last_part = p + 1 == n_part;
+  const int stage_lo = last_part ? N : j_hi;
+  const uint4* wk = stage + ((size_t)inst * (n_part - 1) + p) * 2 * (size_t)B * ROW_U4;
   float qf[G][VEC];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -169,92 +186,110 @@ __global__ __launch_bounds__(kCompBlock) void compact_decode_kernel(
 #pragma unroll
     for (int e = 0; e < VEC; ++e) o[g][e] = 0.f;
   }
-  __syncthreads();
-  const int start = s_start;
-  // register stages: chunk c in (ak, av), c+1 in (bk, bv), c+2 in (ck, cv)
-  uint4 ak[kPasses], av[kPasses], bk[kPasses], bv[kPasses], ck[kPasses], cv[kPasses];
-  auto load = [&](int c0, uint4 (&rk)[kPasses], uint4 (&rv)[kPasses]) {
-#pragma unroll
-    for (int u = 0; u < kPasses; ++u) {
-      const int j = min(c0 + row0 + u * kRowsPerPass, K - 1);
-      const size_t off = (size_t)s_src[j] * ROW_U4 + col;
-      rk[u] = kb[off];
-      rv[u] = vb[off];
-    }
+  struct Rows {
+    uint4 k[kPasses], v[kPasses];
   };
-  const int last = (K - 1) / CHUNK * CHUNK;             // first row of the last chunk
-  load(0, ak, av);
-  load(min(CHUNK, last), bk, bv);
-  for (int c0 = 0; c0 < K; c0 += CHUNK) {
-    load(min(c0 + 2 * CHUNK, last), ck, cv);           // two chunks ahead (the last repeats)
-    // this thread's loads of chunk c0 are done (only the next two chunks'
-    // 4*kPasses loads may remain), then every thread's are
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (4 * kPasses));   // vmcnt(4*kPasses)
+  Rows ra, rb, rc;
+  for (int seg = j_lo; seg < j_hi; seg += kMapRows) {
+    const int seg_hi = min(j_hi, seg + kMapRows);
+    __syncthreads();                                   // the last segment's map is read
+    for (int i = seg + threadIdx.x; i < seg_hi; i += kCompBlock) s_src[i - seg] = clamp_slot(s[i], N);
     __syncthreads();
-    // move the rows of this chunk that are not already in place
-    if (c0 + CHUNK > start) {
+    auto load = [&](int c0, Rows& r) {
 #pragma unroll
       for (int u = 0; u < kPasses; ++u) {
-        const int j = c0 + row0 + u * kRowsPerPass;
-        if (j < K && j >= start) {
-          const size_t off = (size_t)j * ROW_U4 + col;
-          kb[off] = ak[u];
-          vb[off] = av[u];
+        const int sj = s_src[min(c0 + row0 + u * kRowsPerPass, seg_hi - 1) - seg];
+        const bool staged = sj >= stage_lo;
+        const size_t off = (size_t)(staged ? min(sj - stage_lo, B - 1) : sj) * ROW_U4 + col;
+        r.k[u] = (staged ? wk : kb)[off];
+        r.v[u] = (staged ? wk + (size_t)B * ROW_U4 : vb)[off];
+      }
+    };
+    const int last = seg + (seg_hi - 1 - seg) / CHUNK * CHUNK;   // first row of the last chunk
+    bool moved = false;                                  // the chunk before was stored
+    // chunk c0 is in `cur`; two chunks ahead go to `next` (the last repeats)
+    auto step = [&](int c0, const Rows& cur, Rows& next) {
+      load(min(c0 + 2 * CHUNK, last), next);
+      // this thread's loads of chunk c0 are done: only the next two chunks'
+      // 4*kPasses loads may remain, and what the chunk before (a full one)
+      // stored between them; then every thread's are
+      constexpr int kLoads = 4 * kPasses, kScores = CARRY ? kPasses : 0;
+      if (c0 == seg) __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);
+      else if (!moved) __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads + kScores));
+      else __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads + kScores + 2 * kPasses));
+      __syncthreads();
+      // store the chunk unless every row is in place: src[j] - j never falls
+      const bool full = c0 + CHUNK <= seg_hi;
+      const int j_end = min(c0 + CHUNK, seg_hi) - 1;
+      moved = __builtin_amdgcn_readfirstlane(s_src[j_end - seg]) != j_end;
+      if (moved) {
+#pragma unroll
+        for (int u = 0; u < kPasses; ++u) {
+          const int j = c0 + row0 + u * kRowsPerPass;
+          if (full || j < seg_hi) {
+            const size_t off = (size_t)j * ROW_U4 + col;
+            kb[off] = cur.k[u];
+            vb[off] = cur.v[u];
+          }
         }
       }
-    }
-    // decode: scores of the rows, one online-softmax update per chunk
-    float sc[kPasses][G];
+      // decode: scores of the rows, one online-softmax update per chunk
+      float sc[kPasses][G];
 #pragma unroll
-    for (int u = 0; u < kPasses; ++u) {
-      float kf[VEC];
-      Vec16<T>::unpack(ak[u], kf);
-      const bool ok = c0 + row0 + u * kRowsPerPass < K;
+      for (int u = 0; u < kPasses; ++u) {
+        float kf[VEC];
+        Vec16<T>::unpack(cur.k[u], kf);
+        const bool ok = c0 + row0 + u * kRowsPerPass < seg_hi;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float acc = 0.f;
+        for (int g = 0; g < G; ++g) {
+          float acc = 0.f;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc = __builtin_fmaf(qf[g][e], kf[e], acc);
-        acc = lanes_sum<ROW_U4>(acc);
-        sc[u][g] = ok ? acc : -INFINITY;
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float mn = m[g];
-#pragma unroll
-      for (int u = 0; u < kPasses; ++u) mn = fmaxf(mn, sc[u][g]);
-      const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
-      l[g] *= alpha;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) o[g][e] *= alpha;
-      m[g] = mn;
-    }
-#pragma unroll
-    for (int u = 0; u < kPasses; ++u) {
-      float vf[VEC];
-      Vec16<T>::unpack(av[u], vf);
-      if (CARRY) {
-        // the value score of compacted row j, which the next round's candidates
-        // keep unchanged (only the buffer slots are written until then)
-        const float val = row_value_score<VEC, ROW_U4>(vf, value_kind);
-        const int j = c0 + row0 + u * kRowsPerPass;
-        if (col == 0 && j < K) vrange[(size_t)inst * K + j] = val;
+          for (int e = 0; e < VEC; ++e) acc = __builtin_fmaf(qf[g][e], kf[e], acc);
+          acc = lanes_sum<ROW_U4>(acc);
+          sc[u][g] = ok ? acc : -INFINITY;
+        }
       }
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const float p = __builtin_amdgcn_exp2f(sc[u][g] - m[g]);
-        l[g] += p;
+        float mn = m[g];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) o[g][e] = __builtin_fmaf(p, vf[e], o[g][e]);
+        for (int u = 0; u < kPasses; ++u) mn = fmaxf(mn, sc[u][g]);
+        const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
+        l[g] *= alpha;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o[g][e] *= alpha;
+        m[g] = mn;
       }
-    }
 #pragma unroll
-    for (int u = 0; u < kPasses; ++u) {
-      ak[u] = bk[u];
-      av[u] = bv[u];
-      bk[u] = ck[u];
-      bv[u] = cv[u];
+      for (int u = 0; u < kPasses; ++u) {
+        float vf[VEC];
+        Vec16<T>::unpack(cur.v[u], vf);
+        if (CARRY) {
+          // the value score of compacted row j, which the next round's candidates
+          // keep unchanged (only the buffer slots are written until then)
+          const float val = row_value_score<VEC, ROW_U4>(vf, value_kind);
+          const int j = c0 + row0 + u * kRowsPerPass;
+          if (col == 0 && j < seg_hi) vrange[(size_t)inst * K + j] = val;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const float pr = __builtin_amdgcn_exp2f(sc[u][g] - m[g]);
+          l[g] += pr;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[g][e] = __builtin_fmaf(pr, vf[e], o[g][e]);
+        }
+      }
+    };
+    load(seg, ra);
+    __builtin_amdgcn_sched_barrier(0);
+    load(min(seg + CHUNK, last), rb);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int c0 = seg; c0 < seg_hi; c0 += 3 * CHUNK) {
+      step(c0, ra, rc);
+      if (c0 + CHUNK >= seg_hi) break;
+      step(c0 + CHUNK, rb, ra);
+      if (c0 + 2 * CHUNK >= seg_hi) break;
+      step(c0 + 2 * CHUNK, rc, rb);
     }
   }
   // merge the row groups of each wave (lane bits above log2(ROW_U4)), fixed order
@@ -299,29 +334,46 @@ __global__ __launch_bounds__(kCompBlock) void compact_decode_kernel(
       lt += s_ml[w][g][1] * a;
       ot += s_o[w][g][dd] * a;
     }
-    store_out<T>(out + ((size_t)inst * G + g) * D + dd, ot / lt);
+    if (n_part == 1) {
+      store_out<T>(out + ((size_t)inst * G + g) * D + dd, ot / lt);
+    } else {
+      float* pp = part + (((size_t)inst * n_part + p) * G + g) * (kPartHead + D);
+      pp[kPartHead + dd] = ot;
+      if (dd == 0) *reinterpret_cast<float4*>(pp) = make_float4(mn, lt, mn, lt);
+    }
   }
 }
 
+struct CompactDecodeArgs {
+  uint4 *k, *v;
+  const int32_t* src;
+  int n_inst, K, B, G;
+  const void* q;
+  void* out;
+  int value_kind;
+  float* vrange;
+  uint4* stage;
+  float* part;
+};
+
 template <typename T, int D>
-hipError_t launch_cd_d(uint4* k, uint4* v, const int32_t* src, int n_inst, int K, int B, int G,
-                       const void* q, void* out, int value_kind, float* vrange,
-                       hipStream_t stream) {
+hipError_t launch_cd_d(const CompactDecodeArgs& a, const CompactPlan& pl, hipStream_t stream) {
+  constexpr int kRowU4 = D / Vec16<T>::n;
   const float sl = 1.4426950408889634f / sqrtf((float)D);
-  const T* qq = static_cast<const T*>(q);
-  T* oo = static_cast<T*>(out);
-#define VASE_CD(GG)                                                                          \
-  case GG:                                                                                   \
-    if (vrange)                                                                              \
-      hipLaunchKernelGGL((compact_decode_kernel<T, D, GG, true>), dim3(n_inst),              \
-                         dim3(kCompBlock), sizeof(int) * (size_t)K, stream, k, v, src, K, B, \
-                         qq, oo, sl, value_kind, vrange);                                    \
-    else                                                                                     \
-      hipLaunchKernelGGL((compact_decode_kernel<T, D, GG, false>), dim3(n_inst),             \
-                         dim3(kCompBlock), sizeof(int) * (size_t)K, stream, k, v, src, K, B, \
-                         qq, oo, sl, value_kind, vrange);                                    \
-    break;
-  switch (G) {
+  if (pl.n_part > 1)
+    hipLaunchKernelGGL(compact_stage_kernel<kRowU4>, dim3(pl.n_part - 1, a.n_inst), dim3(kCompBlock),
+                       0, stream, a.k, a.v, a.src, a.K, a.B, pl.rows_per_part, pl.n_part, a.stage);
+#define VASE_CD(GG)                                                                             \
+  case GG: {                                                                                    \
+    auto kernel = a.vrange ? compact_decode_kernel<T, D, GG, true>                              \
+                           : compact_decode_kernel<T, D, GG, false>;                            \
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(pl.n_part * a.n_inst)), dim3(kCompBlock), 0,     \
+                       stream, a.k, a.v, a.src, a.K, a.B, pl.rows_per_part, pl.n_part, a.stage, \
+                       static_cast<const T*>(a.q), static_cast<T*>(a.out), a.part, sl,          \
+                       a.value_kind, a.vrange);                                                 \
+    break;                                                                                      \
+  }
+  switch (a.G) {
     VASE_CD(1) VASE_CD(2) VASE_CD(3) VASE_CD(4) VASE_CD(5) VASE_CD(6) VASE_CD(7) VASE_CD(8)
     default: return hipErrorInvalidValue;
   }
@@ -360,20 +412,53 @@ CompactPlan compact_plan(int dtype, int n_inst, int K, int B, int d) {
   return pl;
 }
 
+size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
+  const CompactPlan cp = compact_plan(dtype, n_inst, K, B, d);
+  if (cp.n_part == 1 && K <= kCompactOneMaxK) return 0;
+  const size_t dec = decode_plan(dtype, n_inst, K, B, d, G, K, K).bytes;
+  return cp.bytes > dec ? cp.bytes : dec;
+}
+
+// Parts per instance for about 512 workgroups (two to a CU; 256 and 1024 are
+// within 5 % of it from 64 to 576 instances), of at least 256 rows: each part
+// but the last stages up to B rows, which are copied once more.  64 instances of
+// 4096 rows and 128 staged: 58 us with 8 parts, 66 with 16.  As many parts as
+// the workspace of compact_decode_bytes holds.
+CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G) {
+  const size_t row_bytes = (size_t)d * (dtype == VASE_BF16 ? 2 : 4);
+  const size_t room = compact_decode_bytes(dtype, n_inst, K, B, d, G);
+  const int want = (512 + n_inst - 1) / n_inst;
+  const int most = K / 256 > 0 ? K / 256 : 1;
+  CompactPlan pl;
+  for (int n = want < most ? want : most;; --n) {
+    pl.rows_per_part = ((K + n - 1) / n + 31) / 32 * 32;
+    pl.n_part = (K + pl.rows_per_part - 1) / pl.rows_per_part;
+    pl.bytes = (size_t)n_inst * (pl.n_part - 1) * 2 * (size_t)B * row_bytes;
+    if (pl.n_part == 1) break;
+    pl.off_part = pl.bytes;
+    pl.bytes += (size_t)n_inst * pl.n_part * G * (kPartHead + d) * sizeof(float);
+    if (pl.bytes <= room) break;
+  }
+  return pl;
+}
+
 hipError_t launch_compact_decode(void* k, void* v, int dtype, int n_inst, int K, int B, int d,
                                  const int32_t* src, const void* q, int G, void* out,
-                                 int value_kind, float* vrange, hipStream_t stream) {
-  uint4* kk = static_cast<uint4*>(k);
-  uint4* vv = static_cast<uint4*>(v);
-  const int vk = value_kind;
+                                 int value_kind, float* vrange, void* ws, const CompactPlan& pl,
+                                 hipStream_t stream) {
+  const CompactDecodeArgs a{static_cast<uint4*>(k), static_cast<uint4*>(v), src, n_inst, K, B, G, q,
+                            out, value_kind, vrange, static_cast<uint4*>(ws),
+                            reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_part)};
+  hipError_t e = hipErrorInvalidValue;
   if (dtype == VASE_BF16) {
-    if (d == 128) return launch_cd_d<bf16_t, 128>(kk, vv, src, n_inst, K, B, G, q, out, vk, vrange, stream);
-    if (d == 64) return launch_cd_d<bf16_t, 64>(kk, vv, src, n_inst, K, B, G, q, out, vk, vrange, stream);
+    if (d == 128) e = launch_cd_d<bf16_t, 128>(a, pl, stream);
+    if (d == 64) e = launch_cd_d<bf16_t, 64>(a, pl, stream);
   } else {
-    if (d == 128) return launch_cd_d<float, 128>(kk, vv, src, n_inst, K, B, G, q, out, vk, vrange, stream);
-    if (d == 64) return launch_cd_d<float, 64>(kk, vv, src, n_inst, K, B, G, q, out, vk, vrange, stream);
+    if (d == 128) e = launch_cd_d<float, 128>(a, pl, stream);
+    if (d == 64) e = launch_cd_d<float, 64>(a, pl, stream);
   }
-  return hipErrorInvalidValue;
+  if (e != hipSuccess || pl.n_part == 1) return e;
+  return launch_decode_combine(a.part, dtype, n_inst, d, G, pl.n_part, out, stream);
 }
 
 hipError_t launch_compact(void* k, void* v, int dtype, int n_inst, int K, int B, int d,

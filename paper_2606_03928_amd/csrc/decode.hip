@@ -18,7 +18,6 @@
 // split per instance, half of the grid), and each of its waves keeps the
 // normaliser of the rows below n_persist beside the full one.  A split's
 // partial is (m, l, m_p, l_p, o[D]): the full state and the persistent one.
-constexpr int kPartHead = 4;   // floats ahead of o[D] in a split's partial
 #include "vase_internal.hpp"
 #include "vase.h"
 
@@ -608,6 +607,18 @@ hipError_t launch_decode(const void* k, const void* v, const void* q, int dtype,
     if (d == 64) return launch_d<float, 64>(a, G, w, plan, stream);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_decode_combine(const float* part, int dtype, int n_inst, int d, int G, int n_split,
+                                 void* out, hipStream_t stream) {
+  if (dtype == VASE_BF16) {
+    if (d == 128) launch_combine<bf16_t, 128>(part, n_split, 0, n_inst, G, out, nullptr, 1, stream);
+    else launch_combine<bf16_t, 64>(part, n_split, 0, n_inst, G, out, nullptr, 1, stream);
+  } else {
+    if (d == 128) launch_combine<float, 128>(part, n_split, 0, n_inst, G, out, nullptr, 1, stream);
+    else launch_combine<float, 64>(part, n_split, 0, n_inst, G, out, nullptr, 1, stream);
+  }
+  return hipGetLastError();
 }
 
 hipError_t decode_scratch(void** ptr) {

@@ -225,24 +225,29 @@ size_t select_lds_bytes(int K, int B);
 struct CompactPlan {
   int n_part;       // destination ranges per instance
   int rows_per_part;
-  size_t bytes;     // staging workspace
+  size_t bytes;     // workspace: staged rows, then (fused with a decode) partials
+  size_t off_part = 0;
 };
 CompactPlan compact_plan(int dtype, int n_inst, int K, int B, int d);
 hipError_t launch_compact(void* k, void* v, int dtype, int n_inst, int K, int B, int d,
                           const int32_t* src, void* ws, const CompactPlan& plan,
                           hipStream_t stream);
 
-// Fused compaction + one decode step; only for plans with one part per instance
-// and K <= kCompactDecodeMaxK (the survivor map is staged in LDS).
-constexpr int kCompactDecodeMaxK = 16384;
+// Fused compaction + one decode step, split into parts like launch_compact; the
+// plan's workspace never exceeds compact_decode_bytes.
 // vrange (nullable): value score of kind value_kind of each compacted row [0, K)
+constexpr int kCompactOneMaxK = 16384;   // no workspace for one part of up to so many rows
+CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G);
+size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G);
 hipError_t launch_compact_decode(void* k, void* v, int dtype, int n_inst, int K, int B, int d,
                                  const int32_t* src, const void* q, int G, void* out,
-                                 int value_kind, float* vrange, hipStream_t stream);
+                                 int value_kind, float* vrange, void* ws, const CompactPlan& plan,
+                                 hipStream_t stream);
 // value scores (Range, L2 or Var) of rows [0, K) of a [n_inst][N][d] cache
 hipError_t launch_value_rows(const void* v, int dtype, int n_inst, int N, int K, int d, int kind,
                              float* out, hipStream_t stream, uint32_t* status = nullptr);
 
+constexpr int kPartHead = 4;   // floats ahead of o[d] in a decode partial: m, l, m_p, l_p
 struct DecodePlan {
   int n_split;      // key splits per instance
   int s1;           // splits over [0, n_persist); the rest cover [n_persist, n_valid)
@@ -270,6 +275,10 @@ hipError_t launch_decode(const void* k, const void* v, const void* q, int dtype,
                          int K, int B, int d, int G, int n_valid, int n_persist, void* out,
                          float* lse, int lse_ld, void* ws, const DecodePlan& plan,
                          hipStream_t stream, const DecodeToken& tok = DecodeToken());
+
+// out from n_split partials (m, l, unused, unused, o[d]) per instance and head
+hipError_t launch_decode_combine(const float* part, int dtype, int n_inst, int d, int G, int n_split,
+                                 void* out, hipStream_t stream);
 
 // The cache under an order map (ord[inst][t] = slot of temporal rank t < K).
 // attn_out[t] = P-wide box filter over temporal ranks of attn_phys[ord[.]];
