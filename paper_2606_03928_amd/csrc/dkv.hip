@@ -30,9 +30,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kDkvBlock = 256;
-constexpr int kDkvTilesPerWave = 8;          // 32-row tiles per wave
-constexpr int kDkvRowsPerWave = 32 * kDkvTilesPerWave;
-constexpr int kDkvRowsPerBlock = kDkvRowsPerWave * (kDkvBlock / kWave);
 constexpr int kDkvMaxR = 32;
 
 __global__ __launch_bounds__(kDkvBlock) void dkv_projection_kernel(int n_inst, uint32_t inst_base,
@@ -53,74 +50,79 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
   lo = (__bf16)(x - (float)hi);
 }
 
-// One block: kDkvRowsPerBlock consecutive candidate rows of one instance.  With
-// dlog given, the rows run to N (the buffer included) and the block also writes
-// the decode queries' logits dlog[inst][h][row] = qdec[inst][h] . k_row (h < G)
-// from the key rows it holds: the G queries are the A operand of one more
-// 32x32x16 MFMA chain per tile, the rows the B operand as for the projection.
+// One block: `tiles` consecutive 32-row tiles of one instance, wave w taking
+// tiles w, w + 4, ...  With dlog given, the rows run to N (the buffer included)
+// and the block also writes the decode queries' logits dlog[inst][h][row] =
+// qdec[inst][h] . k_row (h < G) from the key rows it holds: the G queries are the
+// A operand of one more 32x32x16 MFMA chain per tile.  (As spare rows of the
+// projection's head operand they would be free, but the tail chain would add
+// 0 * k to them, which is not 0 for an infinite k.)
 template <int D>
 __global__ __launch_bounds__(kDkvBlock) void dkv_score_mfma_kernel(
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, const float* __restrict__ g,
-    int N, int K, int r, int blocks_per_inst, float* __restrict__ out,
+    int N, int K, int r, int blocks_per_inst, int tiles, float* __restrict__ out,
     const uint16_t* __restrict__ qdec, int G, float* __restrict__ dlog) {
   constexpr int KS = D / 16;
-  __shared__ float sg[D * kDkvMaxR];
   __shared__ bf16x8_t sa[3][KS][kWave];   // [G^T head, G^T tail, decode queries][step][lane]
-  const uint32_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
-  const int inst = (int)(lb / (uint32_t)blocks_per_inst);
-  const int rb = (int)(lb % (uint32_t)blocks_per_inst);
+  // blocks in dispatch order: what is resident covers one stretch of memory (an
+  // eighth of the instances to each XCD: 272 against 263 us)
+  const int inst = (int)(blockIdx.x / (unsigned)blocks_per_inst);
+  const int rb = (int)(blockIdx.x % (unsigned)blocks_per_inst);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, half = lane / 32;
-  // G of this instance into LDS as [d][32], columns >= r zero
+  // A operands, the same for every wave: G^T (32 projection columns x D, columns
+  // >= r zero), head and tail, and the decode queries, staged once per block as
+  // per-lane fragments read at each step (in registers they would take 96
+  // VGPRs).  The contraction index is permuted identically in both operands:
+  // lane half h, step ks holds elements [16*ks + 8*h, +8), so that the two lanes
+  // of a row read 32 adjacent bytes in one load.
   const float* gi = g + (size_t)inst * D * r;
-  for (int t = threadIdx.x; t < D * kDkvMaxR; t += kDkvBlock) {
-    const int a = t / kDkvMaxR, b = t % kDkvMaxR;
-    sg[t] = b < r ? gi[a * r + b] : 0.f;
-  }
-  __syncthreads();
-  // A operands, the same for every wave: G^T (32 projection columns x D), head
-  // and tail, and the decode queries (row = head, clamped), staged once per
-  // block as per-lane fragments read at each step (in registers they would
-  // take 96 VGPRs).  The contraction index is permuted identically in both
-  // operands: lane half h, step ks holds elements [16*ks + 8*h, +8), so that
-  // the two lanes of a row read 32 adjacent bytes in one load (with the
-  // halves 128 bytes apart, every load touched 64 lines for 16 bytes each).
+  const uint16_t* qi = dlog ? qdec + (size_t)inst * G * D : nullptr;
   const int col = lane % 32;
-  for (int t = threadIdx.x; t < KS * kWave; t += kDkvBlock) {
-    const int ks = t / kWave, l = t % kWave, c = l % 32, h = l / 32;
-    bf16x8_t fh, fl;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      __bf16 hi, lo;
-      split_bf16(sg[(16 * ks + 8 * h + e) * kDkvMaxR + c], hi, lo);
-      fh[e] = hi;
-      fl[e] = lo;
+  for (int i = 0; i < (KS * kWave + kDkvBlock - 1) / kDkvBlock; ++i) {
+    const int t = (int)threadIdx.x + i * kDkvBlock;
+    const int ks = t / kWave, c = t % 32, d0 = 16 * ks + 8 * (t % kWave / 32);
+    bf16x8_t fh = {}, fl = {};
+    if (c < r) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        __bf16 hi, lo;
+        split_bf16(gi[(d0 + e) * r + c], hi, lo);
+        fh[e] = hi;
+        fl[e] = lo;
+      }
     }
-    sa[0][ks][l] = fh;
-    sa[1][ks][l] = fl;
+    sa[0][ks][t % kWave] = fh;
+    sa[1][ks][t % kWave] = fl;
     if (dlog)
-      sa[2][ks][l] = reinterpret_cast<const bf16x8_t*>(
-          qdec + ((size_t)inst * G + min(c, G - 1)) * D + 8 * h)[2 * ks];
+      sa[2][ks][t % kWave] = *reinterpret_cast<const bf16x8_t*>(qi + (size_t)min(c, G - 1) * D + d0);
   }
   __syncthreads();
   const int rows = dlog ? N : K;
   const uint16_t* kinst = k + (size_t)inst * N * D;
   const uint16_t* vinst = v + (size_t)inst * N * D;
   float* oinst = out + (size_t)inst * K;
-  const int row_base = rb * kDkvRowsPerBlock + wave * kDkvRowsPerWave;
-  // tile t of this wave: rows row_base + 32 t + [0, 32); rows past K re-read
-  // row K-1 and are not stored.  All 2*KS loads of a tile are issued before its
-  // first MFMA (one wait per tile); the other waves of the SIMD cover it.
-  auto load_tile = [&](int t, bf16x8_t (&kb)[KS], bf16x8_t (&vb)[KS]) {
-    const int rr = min(row_base + t * 32 + col, rows - 1);
+  const int row_base = rb * tiles * 32;
+  const int nt = min(tiles, (rows - row_base + 31) / 32);
+  // All 2*KS loads of a tile are issued before its first MFMA, a row's pieces
+  // one after the other: the four loads of a 128-byte line meet it in L1 (loads
+  // that skip L1 take 369 us for 264).  Rows past the last re-read it and are not
+  // stored.  12 waves of 16 KB keep 49 MB in flight over the chip, so what is
+  // left above the copy rate is how the memory takes this pattern: 1.28 GB (576
+  // instances of 4224 rows, with logits) 293 -> 263 us, 4.9 TB/s; 8 instances
+  // of 2176 rows, which fill the chip with blocks of 4 tiles, 24.7 -> 8.4 us.
+  for (int t = wave; t < nt; t += kDkvBlock / kWave) {
+    const int row = row_base + t * 32 + col;
+    const int rr = min(row, rows - 1);
     const bf16x8_t* kr = reinterpret_cast<const bf16x8_t*>(kinst + (size_t)rr * D + 8 * half);
     const bf16x8_t* vr = reinterpret_cast<const bf16x8_t*>(vinst + (size_t)rr * D + 8 * half);
+    bf16x8_t kb[KS], vb[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      kb[ks] = kr[2 * ks];
-      vb[ks] = vr[2 * ks];
-    }
-  };
-  auto tile_step = [&](int t, const bf16x8_t (&kb)[KS], const bf16x8_t (&vb)[KS]) {
+    for (int ks = 0; ks < KS; ++ks) kb[ks] = kr[2 * ks];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) vb[ks] = vr[2 * ks];
+    __builtin_amdgcn_sched_barrier(0);
     f32x16_t pk = f32x16_t{}, pv = f32x16_t{};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -139,29 +141,21 @@ __global__ __launch_bounds__(kDkvBlock) void dkv_score_mfma_kernel(
     }
     lk += __shfl_xor(lk, 32, kWave);
     lv += __shfl_xor(lv, 32, kWave);
-    const int row = row_base + t * 32 + col;
     if (half == 0 && row < K) oinst[row] = lk * lv;
     if (dlog) {
-      f32x16_t pq = f32x16_t{};
+      pk = f32x16_t{};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        pq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa[2][ks][lane], kb[ks], pq, 0, 0, 0);
+        pk = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sa[2][ks][lane], kb[ks], pk, 0, 0, 0);
       // lane holds head 8(e/4) + 4h + e%4 of row `col`
       if (row < N) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int h = 8 * (e / 4) + 4 * half + e % 4;
-          if (h < G) dlog[((size_t)inst * G + h) * N + row] = pq[e];
+          if (h < G) dlog[((size_t)inst * G + h) * N + row] = pk[e];
         }
       }
     }
-  };
-  const int nt = min(kDkvTilesPerWave, (rows - row_base + 31) / 32);
-  for (int t = 0; t < nt; ++t) {
-    bf16x8_t kb[KS], vb[KS];
-    load_tile(t, kb, vb);
-    __builtin_amdgcn_sched_barrier(0);
-    tile_step(t, kb, vb);
   }
 }
 
@@ -208,17 +202,25 @@ hipError_t launch_dkv_score(const void* k, const void* v, const float* g, int dt
                             float* dec_logits, hipStream_t stream) {
   const int N = K + B;
   if (dtype == VASE_BF16) {
-    const int bpi = ((dec_logits ? N : K) + kDkvRowsPerBlock - 1) / kDkvRowsPerBlock;
+    // blocks of at least 32 tiles (8 a wave, over which the operands' staging is
+    // spread), evenly split, so that no block is a remainder; down to one tile a
+    // wave where that leaves some of the 768 places (three blocks to a CU) empty
+    const int nt = ((dec_logits ? N : K) + 31) / 32;
+    int want = (768 + n_inst - 1) / n_inst;
+    want = want < nt / 4 ? want : nt / 4;
+    want = want > nt / 32 ? want : nt / 32;
+    const int tiles = want > 1 ? (nt + want - 1) / want : nt;
+    const int bpi = (nt + tiles - 1) / tiles;
     const uint16_t* qd = static_cast<const uint16_t*>(q_dec);
     const unsigned grid = (unsigned)(n_inst * bpi);
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     if (d == 128)
       hipLaunchKernelGGL((dkv_score_mfma_kernel<128>), dim3(grid), dim3(kDkvBlock), 0, stream, kk,
-                         vv, g, N, K, r, bpi, out, qd, G, dec_logits);
+                         vv, g, N, K, r, bpi, tiles, out, qd, G, dec_logits);
     else
       hipLaunchKernelGGL((dkv_score_mfma_kernel<64>), dim3(grid), dim3(kDkvBlock), 0, stream, kk,
-                         vv, g, N, K, r, bpi, out, qd, G, dec_logits);
+                         vv, g, N, K, r, bpi, tiles, out, qd, G, dec_logits);
   } else {
     const dim3 grid((K + kDkvBlock - 1) / kDkvBlock, n_inst);
     const float* kk = static_cast<const float*>(k);
