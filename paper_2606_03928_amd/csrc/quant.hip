@@ -14,9 +14,14 @@
 // of 1/Delta), which lies within 3 ulp of the correctly rounded (x - z) / Delta;
 // the quotient is at most 2^b - 1 <= 255, so 3 ulp are below 2^-13, and when
 // the product is more than 2^-12 away from the nearest half-integer both round
-// to the same integer.  Otherwise (or for a non-finite reciprocal) the element
-// takes the IEEE divide.  The clamp to [0, 2^b - 1] needs no upper bound: with
-// x - z <= Range (rounding is monotonic) the product stays below 2^b - 1/2.
+// to the same integer.  Otherwise (or for a non-finite product) the element takes
+// the IEEE divide.  On the coarse grid of bf16 inputs one element in several
+// hundred is an exact tie, so that some lane of a wave has one in most rows: a
+// branch per element (12 % taken) costs less than one per row with the divides of
+// all eight (250 us for 193, 576 instances of 4096 rows at 4 bits), also with the
+// ties told apart from their residuals first (254 us).  The clamp to
+// [0, 2^b - 1] needs no upper bound: with x - z <= Range (rounding is monotonic)
+// the product stays below 2^b - 1/2.
 //
 // Layout: a row of D elements is spread over LPR = D*e/16 lanes, 16 bytes each;
 // a group covers GROUP/VEC consecutive lanes, so its min and max are butterfly
@@ -34,17 +39,22 @@ namespace vase {
 namespace {
 
 constexpr int kQBlock = 256;
-constexpr int kQRowsPerBlock = 64;
 
-template <int LANES, bool MAX>
-__device__ __forceinline__ float xor_reduce(float x, int from) {
-  // reduce over lane bits [log2(from), log2(LANES)): from = 1 reduces LANES lanes
-#pragma unroll
-  for (int o = 1; o < LANES; o <<= 1) {
-    if (o < from) continue;
-    const float y = __shfl_xor(x, o, kWave);
-    x = MAX ? fmaxf(x, y) : x + y;
-  }
+// x reduced over lane bits [log2(FROM), log2(LANES)), the lanes below FROM being
+// equal already: every lane of the LANES ends with the result.  DPP moves (lane^1,
+// lane^2, mirrors within 8 and 16), which need no LDS crossbar.
+template <int LANES, bool MAX, int FROM = 1>
+__device__ __forceinline__ float xor_reduce(float x) {
+  auto with = [](float a, float y) { return MAX ? fmaxf(a, y) : a + y; };
+#define VASE_DPP(o, c)                                                                         \
+  if (o >= FROM && o < LANES)                                                                  \
+    x = with(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), c, 0xf, 0xf, false)))
+  VASE_DPP(1, 0xB1);
+  VASE_DPP(2, 0x4E);
+  VASE_DPP(4, 0x141);
+  VASE_DPP(8, 0x140);
+#undef VASE_DPP
+  if (LANES == 32 && FROM <= 16) x = with(x, __shfl_xor(x, 16, kWave));
   return x;
 }
 
@@ -93,17 +103,35 @@ __device__ __forceinline__ uint4 pack16<bf16_t>(const float* r) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// the code of one element (see the file comment for why the fast quotient is safe)
+// the code of one element (see the file comment for why the fast quotient is
+// safe); inv = 1 / delta, 0 unless delta > 0
 __device__ __forceinline__ float quant_code(float x, float z, float delta, float inv) {
-  if (!(delta > 0.0f)) return 0.0f;
   const float t = x - z;
-  float q = __builtin_rintf(t * inv);
   const float u = t * inv;
-  if (!(__builtin_fabsf(u - q) <= 0.5f - 0x1p-12f)) q = __builtin_rintf(t / delta);
-  return fmaxf(q, 0.0f);   // also maps a NaN (non-finite inputs) to 0
+  float q = __builtin_rintf(u);
+  // the maximum also maps a NaN (non-finite inputs) to 0
+  if (!(__builtin_fabsf(u - q) <= 0.5f - 0x1p-12f))
+    q = delta > 0.0f ? fmaxf(__builtin_rintf(t / delta), 0.0f) : 0.0f;
+  return q;
 }
 
-template <typename T, int D, int BITS, int GROUP>
+// VEC codes of BITS bits, the first lowest.  As many as fit in 24 bits are summed
+// in fp32 (exactly: they are whole numbers) and converted together.
+template <int VEC, int BITS, typename Packed>
+__device__ __forceinline__ Packed pack_codes(const float (&q)[VEC]) {
+  constexpr int kEach = BITS == 8 ? 2 : 4;
+  Packed packed = 0;
+#pragma unroll
+  for (int e = 0; e < VEC; e += kEach) {
+    float s = q[e + kEach - 1];
+#pragma unroll
+    for (int i = kEach - 2; i >= 0; --i) s = __builtin_fmaf(s, (float)(1 << BITS), q[e + i]);
+    packed |= (Packed)(uint32_t)s << (e * BITS);
+  }
+  return packed;
+}
+
+template <typename T, int D, int BITS, int GROUP, int ROWS>
 __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
     const T* __restrict__ x, int N, int K, uint8_t* __restrict__ codes, float2* __restrict__ params,
     float* __restrict__ range_out, float* __restrict__ mse_out) {
@@ -111,7 +139,7 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
   constexpr int LPR = D / VEC;                 // lanes per row
   constexpr int LPG = GROUP / VEC;             // lanes per group
   constexpr int RPI = kQBlock / LPR;           // rows per block iteration
-  constexpr int ITERS = kQRowsPerBlock / RPI;
+  constexpr int ITERS = ROWS / RPI;
   constexpr int CB = VEC * BITS / 8;           // code bytes per lane
   constexpr int NG = D / GROUP;
   static_assert(LPG >= 1 && LPG <= LPR && CB >= 1, "group must cover whole lanes");
@@ -120,7 +148,7 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
   const int inst = blockIdx.y;
   const int seg = threadIdx.x % LPR;
   const int r_in = threadIdx.x / LPR;
-  const int row0 = blockIdx.x * kQRowsPerBlock;
+  const int row0 = blockIdx.x * ROWS;
   const uint4* xb = reinterpret_cast<const uint4*>(x + (size_t)inst * N * D);
 
   uint4 w[ITERS];
@@ -141,8 +169,8 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
       mn = fminf(mn, f[e]);
       mx = fmaxf(mx, f[e]);
     }
-    const float gmn = -xor_reduce<LPG, true>(-mn, 1);
-    const float gmx = xor_reduce<LPG, true>(mx, 1);
+    const float gmn = -xor_reduce<LPG, true>(-mn);
+    const float gmx = xor_reduce<LPG, true>(mx);
     // Delta = Range / levels, correctly rounded, from the product with the
     // rounded reciprocal and one fma correction: for the divisors 3, 15 and
     // 255 that is the IEEE quotient for every finite Range >= 0 (the host
@@ -151,24 +179,22 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
     const float q0 = range * kRcpLevels;
     const float qc = __builtin_fmaf(__builtin_fmaf(-q0, levels, range), kRcpLevels, q0);
     const float delta = q0 < INFINITY ? qc : q0;
-    const float inv = __builtin_amdgcn_rcpf(delta);
+    const float inv = delta > 0.0f ? __builtin_amdgcn_rcpf(delta) : 0.0f;
     using Packed = typename std::conditional<VEC * BITS <= 32, uint32_t, uint64_t>::type;
-    Packed packed = 0;
-    float ss = 0.0f;
+    float q[VEC], ss = 0.0f;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      const float q = quant_code(f[e], gmn, delta, inv);
-      packed |= (Packed)(uint32_t)q << (e * BITS);
-      const float diff = f[e] - __builtin_fmaf(q, delta, gmn);
+      q[e] = quant_code(f[e], gmn, delta, inv);
+      const float diff = f[e] - __builtin_fmaf(q[e], delta, gmn);
       ss = __builtin_fmaf(diff, diff, ss);
     }
     // the row's Range and squared error over all LPR lanes
-    const float rmn = -xor_reduce<LPR, true>(-gmn, LPG);
-    const float rmx = xor_reduce<LPR, true>(gmx, LPG);
-    ss = xor_reduce<LPR, false>(ss, 1);
+    const float rmn = -xor_reduce<LPR, true, LPG>(-gmn);
+    const float rmx = xor_reduce<LPR, true, LPG>(gmx);
+    ss = xor_reduce<LPR, false>(ss);
     if (row < K) {
       const size_t ri = (size_t)inst * K + row;
-      CodeStore<CB>::put(codes + ri * (D * BITS / 8) + seg * CB, packed);
+      CodeStore<CB>::put(codes + ri * (D * BITS / 8) + seg * CB, pack_codes<VEC, BITS, Packed>(q));
       if (seg % LPG == 0) params[ri * NG + seg / LPG] = make_float2(delta, gmn);
       if (seg == 0) {
         if (range_out) range_out[ri] = rmx - rmn;
@@ -178,7 +204,7 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
   }
 }
 
-template <typename T, int D, int BITS, int GROUP>
+template <typename T, int D, int BITS, int GROUP, int ROWS>
 __global__ __launch_bounds__(kQBlock) void dequant_rows_kernel(
     const uint8_t* __restrict__ codes, const float2* __restrict__ params, int N, int K,
     T* __restrict__ out) {
@@ -186,14 +212,14 @@ __global__ __launch_bounds__(kQBlock) void dequant_rows_kernel(
   constexpr int LPR = D / VEC;
   constexpr int LPG = GROUP / VEC;
   constexpr int RPI = kQBlock / LPR;
-  constexpr int ITERS = kQRowsPerBlock / RPI;
+  constexpr int ITERS = ROWS / RPI;
   constexpr int CB = VEC * BITS / 8;
   constexpr int NG = D / GROUP;
   constexpr uint32_t kMask = (1u << BITS) - 1u;
   const int inst = blockIdx.y;
   const int seg = threadIdx.x % LPR;
   const int r_in = threadIdx.x / LPR;
-  const int row0 = blockIdx.x * kQRowsPerBlock;
+  const int row0 = blockIdx.x * ROWS;
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int row = row0 + it * RPI + r_in;
@@ -237,24 +263,27 @@ __global__ __launch_bounds__(NWV * kWave) void quant_reserve_kernel(
   constexpr int kU4 = D * (int)sizeof(T) / 16;
   const uint4* xb = reinterpret_cast<const uint4*>(x + (size_t)inst * N * D);
   uint4* hb = reinterpret_cast<uint4*>(hp_rows + (size_t)inst * Nv * D);
+#pragma unroll 4
   for (int t = threadIdx.x; t < Nv * kU4; t += NT) {
     const int s = order[t / kU4];
     hb[t] = xb[(size_t)s * kU4 + t % kU4];
   }
 }
 
+// One 16-byte piece per thread: two latencies, the index and the row (a workgroup
+// per instance took 14 us for 576 instances of 128 rows).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void dequant_reserve_kernel(const T* __restrict__ hp_rows,
                                                              const int32_t* __restrict__ hp_idx,
-                                                             int K, int Nv, int N,
+                                                             int K, int Nv, int N, size_t pieces,
                                                              T* __restrict__ out) {
   constexpr int kU4 = D * (int)sizeof(T) / 16;
-  const int inst = blockIdx.x;
-  const uint4* hb = reinterpret_cast<const uint4*>(hp_rows + (size_t)inst * Nv * D);
-  uint4* ob = reinterpret_cast<uint4*>(out + (size_t)inst * N * D);
-  for (int t = threadIdx.x; t < Nv * kU4; t += 256) {
-    const int s = hp_idx[(size_t)inst * Nv + t / kU4];
-    if (s >= 0 && s < K) ob[(size_t)s * kU4 + t % kU4] = hb[t];
+  for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < pieces; t += (size_t)gridDim.x * 256) {
+    const size_t row = t / kU4;
+    const int s = hp_idx[row];
+    const uint4 x = reinterpret_cast<const uint4*>(hp_rows)[t];
+    if (s >= 0 && s < K)
+      reinterpret_cast<uint4*>(out)[(row / (size_t)Nv * N + s) * kU4 + t % kU4] = x;
   }
 }
 
@@ -274,11 +303,11 @@ struct QuantArgs {
   int n_inst, N, K, Nv;
 };
 
-template <typename T, int D, int BITS, int GROUP>
-hipError_t run_bg(const QuantArgs& a, bool quant, hipStream_t s) {
-  const dim3 grid((a.K + kQRowsPerBlock - 1) / kQRowsPerBlock, a.n_inst);
+template <typename T, int D, int BITS, int GROUP, int ROWS>
+hipError_t run_rows(const QuantArgs& a, bool quant, hipStream_t s) {
+  const dim3 grid((a.K + ROWS - 1) / ROWS, a.n_inst);
   if (quant) {
-    hipLaunchKernelGGL((quant_rows_kernel<T, D, BITS, GROUP>), grid, dim3(kQBlock), 0, s,
+    hipLaunchKernelGGL((quant_rows_kernel<T, D, BITS, GROUP, ROWS>), grid, dim3(kQBlock), 0, s,
                        static_cast<const T*>(a.x), a.N, a.K, a.codes,
                        reinterpret_cast<float2*>(a.params), a.range, a.mse);
     if (a.Nv > 0) {
@@ -291,16 +320,27 @@ hipError_t run_bg(const QuantArgs& a, bool quant, hipStream_t s) {
       });
     }
   } else {
-    hipLaunchKernelGGL((dequant_rows_kernel<T, D, BITS, GROUP>), grid, dim3(kQBlock), 0, s,
+    hipLaunchKernelGGL((dequant_rows_kernel<T, D, BITS, GROUP, ROWS>), grid, dim3(kQBlock), 0, s,
                        a.codes_in, reinterpret_cast<const float2*>(a.params_in), a.N, a.K,
                        static_cast<T*>(a.out));
     if (a.Nv > 0) {
-      hipLaunchKernelGGL((dequant_reserve_kernel<T, D>), dim3(a.n_inst), dim3(256), 0, s,
-                         static_cast<const T*>(a.hp_in), a.idx_in, a.K, a.Nv, a.N,
-                         static_cast<T*>(a.out));
+      const size_t pieces = (size_t)a.n_inst * a.Nv * (D * sizeof(T) / 16);
+      const size_t blocks = (pieces + 255) / 256, most = (size_t)1 << 20;
+      hipLaunchKernelGGL((dequant_reserve_kernel<T, D>), dim3((unsigned)(blocks < most ? blocks : most)),
+                         dim3(256), 0, s, static_cast<const T*>(a.hp_in), a.idx_in, a.K, a.Nv, a.N,
+                         pieces, static_cast<T*>(a.out));
     }
   }
   return hipGetLastError();
+}
+
+// 64 rows per block (four 16-byte pieces per thread in flight, bf16) where that
+// fills the chip's places (8 blocks to a CU), else 32: 8 instances of 2048 rows
+// 4.9 -> 3.7 us and back 4.1 -> 3.4, but 576 of 4096 178 -> 180 and 155 -> 158.
+template <typename T, int D, int BITS, int GROUP>
+hipError_t run_bg(const QuantArgs& a, bool quant, hipStream_t s) {
+  return (long long)a.n_inst * ((a.K + 63) / 64) >= 2048 ? run_rows<T, D, BITS, GROUP, 64>(a, quant, s)
+                                                         : run_rows<T, D, BITS, GROUP, 32>(a, quant, s);
 }
 
 template <typename T, int D, int BITS>
