@@ -6,9 +6,10 @@
 // [V*t, V*t + V) as 32-bit patterns (non-negative fp32 values order like their
 // bit patterns).  The k-th largest pattern is fixed one bit at a time from the
 // highest bit in which two candidates differ: a bit stays set when at least k
-// candidates are at or above the threshold with it.  Each wave counts with
-// ballots, the per-wave counts meet in LDS (double-buffered, one barrier per
-// bit), and the ties at the threshold are taken in slot order from a
+// candidates are at or above the threshold with it, and the search ends once
+// exactly k are (for values without ties after about log2 K bits of the 20 to 27
+// that differ).  Each wave counts with ballots, the per-wave counts meet in LDS
+// (double-buffered, one barrier per bit), and the ties at the threshold are taken in slot order from a
 // block-wide prefix sum, so the result is unique under (value desc, slot asc)
 // or (value desc, slot desc).
 #pragma once
@@ -35,14 +36,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
 }
 
 // The thread layout for K candidates: V slots per thread, a multiple of 4 (the
-// selection draws one Philox block per 4 slots), over four waves up to
-// K = 6144 and eight beyond (K <= 8192).  f is called with
-// std::integral_constant<int, V> and std::integral_constant<int, NWV>.
+// selection draws one Philox block per 4 slots), in one wave up to K = 512, whose
+// counts need no barrier (2 instances of K = 128: 17.8 -> 6.6 us with the early
+// end, 2304 of K = 512: 46 -> 14 us), over four up to K = 6144 and eight beyond
+// (K <= 8192).  f is called with std::integral_constant<int, V> and
+// std::integral_constant<int, NWV>.
 template <typename F>
 void with_topk_layout(int K, F&& f) {
   static_assert(16 * 8 * kWave >= VASE_MAX_K, "the widest layout covers every K");
   using std::integral_constant;
-  if (K <= 8 * 256)
+  if (K <= 4 * 64)
+    f(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+  else if (K <= 8 * 64)
+    f(integral_constant<int, 8>{}, integral_constant<int, 1>{});
+  else if (K <= 8 * 256)
     f(integral_constant<int, 8>{}, integral_constant<int, 4>{});
   else if (K <= 16 * 256)
     f(integral_constant<int, 16>{}, integral_constant<int, 4>{});
@@ -162,7 +169,8 @@ __device__ void block_select_top_regs(const uint32_t (&v)[V], const uint32_t (&c
   const uint32_t diff = vand ^ vor;
   const int top = diff ? 32 - __clz(diff) : 0;
   uint32_t T = top >= 32 ? 0u : vand & ~((1u << top) - 1u);
-  // T becomes the k-th largest candidate (non-candidates are 0 and never reach
+  // T becomes the k-th largest candidate, or a value that parts it from the next
+  // (non-candidates are 0 and never reach
   // a threshold with a bit set); the counts alternate between two LDS rows, so
   // one barrier per bit separates a row's writes from its reads and rewrites
   int par = 0;
@@ -171,15 +179,19 @@ __device__ void block_select_top_regs(const uint32_t (&v)[V], const uint32_t (&c
     uint32_t cnt = 0;
 #pragma unroll
     for (int i = 0; i < V; ++i) cnt += (uint32_t)__popcll(__ballot(v[i] >= t));
-    if (lane_id() == 0) sh.cnt[par][wave_id()] = cnt;
-    __syncthreads();
-    uint32_t tot = 0;
+    uint32_t tot = cnt;
+    if constexpr (NWV > 1) {
+      if (lane_id() == 0) sh.cnt[par][wave_id()] = cnt;
+      __syncthreads();
+      tot = 0;
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) tot += sh.cnt[par][w];
-    // the same in every lane: keep the threshold in a scalar register
-    tot = __builtin_amdgcn_readfirstlane(tot);
+      for (int w = 0; w < NWV; ++w) tot += sh.cnt[par][w];
+      // the same in every lane: keep the threshold in a scalar register
+      tot = __builtin_amdgcn_readfirstlane(tot);
+      par ^= 1;
+    }
     if (tot >= k) T = t;
-    par ^= 1;
+    if (tot == k) break;                  // the candidates at or above T are the k
   }
   // every candidate above T, and `need` of those equal to T in slot order
   uint32_t gt_t = 0, eq_t = 0;
