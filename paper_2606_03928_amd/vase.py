@@ -19,6 +19,7 @@ Entry points (names as in ``include/vase.h``):
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import re
 import threading
@@ -63,6 +64,8 @@ _lib = None
 def load() -> ctypes.CDLL:
     """Load libvase.so (raises if it has not been built)."""
     global _lib
+    if _lib is not None:        # set once, complete
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib
@@ -154,12 +157,16 @@ def dtype_code(t: torch.dtype) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # an int: the functions' argtypes make a pointer of it
+    return None if t is None else t.data_ptr()
 
 
 def _stream_ptr(device: torch.device, stream: Optional[torch.cuda.Stream]):
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle without a Stream object around it
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
 def _status_ptr(status: Optional[torch.Tensor], device):
@@ -181,6 +188,7 @@ def _dev(t: torch.Tensor, name: str) -> None:
     _require(t.is_contiguous(), "%s must be contiguous" % name)
 
 
+@functools.lru_cache(maxsize=256)   # a function of the sizes alone, asked on every call
 def workspace_bytes(op: int, dtype: torch.dtype, n_inst: int, K: int, B: int, d: int,
                     G: int = 1, w: int = 1) -> int:
     return int(load().vase_workspace_bytes(op, dtype_code(dtype), n_inst, K, B, d, G, w))
