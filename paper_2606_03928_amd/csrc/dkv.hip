@@ -15,7 +15,7 @@
 // operand, split into a bf16 head and tail (G ~ G_hi + G_lo to 2^-16) so that
 // the bf16 rows meet an almost fp32 projection; the accumulator then holds
 // 16 projection coordinates x 1 row per lane and the squared norm is a sum
-// inside the lane plus one exchange.  fp32 caches use one thread per row.
+// inside the lane plus one exchange.  fp32 caches take the fp32 MFMA.
 #include "vase_internal.hpp"
 #include "vase.h"
 
@@ -27,10 +27,10 @@ namespace vase {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kDkvBlock = 256;
-constexpr int kDkvMaxR = 32;
 
 __global__ __launch_bounds__(kDkvBlock) void dkv_projection_kernel(int n_inst, uint32_t inst_base,
                                                                  int dr, int r, uint32_t k0,
@@ -159,31 +159,77 @@ __global__ __launch_bounds__(kDkvBlock) void dkv_score_mfma_kernel(
   }
 }
 
-// fp32 caches: one thread per candidate row, G in LDS.
+// fp32 caches: the same tiles with v_mfma_f32_32x32x2_f32, which multiplies and
+// accumulates in fp32.  A lane holds 4 of every 8 elements of its row and of its
+// projection column, the contraction index permuted alike in both.  A tile takes
+// 2 x D/2 MFMAs of 64 cycles (3.4 us at d = 128 on one SIMD) against 32 KB from
+// memory, so both are near their rates.  One thread per row, which went over the
+// row once per projection column, took 6581 us for 288 instances of 4096 rows
+// at r = 20 (1.21 GB); this takes 228 (5.3 TB/s); 8 instances of 2048 rows 141 -> 9.4 us.
 template <int D>
-__global__ __launch_bounds__(kDkvBlock) void dkv_score_valu_kernel(
+__global__ __launch_bounds__(kDkvBlock, 2) void dkv_score_f32_kernel(
     const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ g, int N,
-    int K, int r, float* __restrict__ out) {
-  __shared__ float sg[D * kDkvMaxR];
-  const int inst = blockIdx.y;
+    int K, int r, int blocks_per_inst, int tiles, float* __restrict__ out) {
+  constexpr int P = D / 8;
+  __shared__ f32x4_t sa[P][kWave];        // G^T, columns >= r zero
+  const int inst = (int)(blockIdx.x / (unsigned)blocks_per_inst);
+  const int rb = (int)(blockIdx.x % (unsigned)blocks_per_inst);
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, half = lane / 32;
+  const int col = lane % 32;
   const float* gi = g + (size_t)inst * D * r;
-  for (int t = threadIdx.x; t < D * r; t += kDkvBlock) sg[t] = gi[t];
-  __syncthreads();
-  const int row = blockIdx.x * kDkvBlock + threadIdx.x;
-  if (row >= K) return;
-  const float* kr = k + ((size_t)inst * N + row) * D;
-  const float* vr = v + ((size_t)inst * N + row) * D;
-  float lk = 0.f, lv = 0.f;
-  for (int b = 0; b < r; ++b) {
-    float pk = 0.f, pv = 0.f;
-    for (int a = 0; a < D; ++a) {
-      pk = __builtin_fmaf(kr[a], sg[a * r + b], pk);
-      pv = __builtin_fmaf(vr[a], sg[a * r + b], pv);
+#pragma unroll
+  for (int i = wave; i < P; i += kDkvBlock / kWave) {
+    f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+    if (col < r) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[c] = gi[(8 * i + 4 * half + c) * r + col];
     }
-    lk = __builtin_fmaf(pk, pk, lk);
-    lv = __builtin_fmaf(pv, pv, lv);
+    sa[i][lane] = x;
   }
-  out[(size_t)inst * K + row] = lk * lv;
+  __syncthreads();
+  const float* kinst = k + (size_t)inst * N * D;
+  const float* vinst = v + (size_t)inst * N * D;
+  float* oinst = out + (size_t)inst * K;
+  const int row_base = rb * tiles * 32;
+  const int nt = min(tiles, (K - row_base + 31) / 32);
+  for (int t = wave; t < nt; t += kDkvBlock / kWave) {
+    const int row = row_base + t * 32 + col;
+    const size_t at = (size_t)min(row, K - 1) * D + 4 * half;   // rows past the last re-read it
+    const f32x4_t* kr = reinterpret_cast<const f32x4_t*>(kinst + at);
+    const f32x4_t* vr = reinterpret_cast<const f32x4_t*>(vinst + at);
+    f32x4_t kb[P], vb[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) kb[i] = kr[2 * i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < P; ++i) vb[i] = vr[2 * i];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16_t pk = f32x16_t{}, pv = f32x16_t{};
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const f32x4_t a = sa[i][lane];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) pk = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c], kb[i][c], pk, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const f32x4_t a = sa[i][lane];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) pv = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c], vb[i][c], pv, 0, 0, 0);
+    }
+    // lane holds projection coordinates 8(e/4) + 4h + e%4 of row `col`; the
+    // padding ones are left out (0 times an infinite element is no 0)
+    float lk = 0.f, lv = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const bool proj = 8 * (e / 4) + 4 * half + e % 4 < r;
+      lk = proj ? __builtin_fmaf(pk[e], pk[e], lk) : lk;
+      lv = proj ? __builtin_fmaf(pv[e], pv[e], lv) : lv;
+    }
+    lk += __shfl_xor(lk, 32, kWave);
+    lv += __shfl_xor(lv, 32, kWave);
+    if (half == 0 && row < K) oinst[row] = lk * lv;
+  }
 }
 
 }  // namespace
@@ -201,36 +247,26 @@ hipError_t launch_dkv_score(const void* k, const void* v, const float* g, int dt
                             int K, int B, int d, int r, float* out, const void* q_dec, int G,
                             float* dec_logits, hipStream_t stream) {
   const int N = K + B;
+  // blocks of at least 32 tiles (8 a wave, over which the operands' staging is
+  // spread), evenly split, so that no block is a remainder; down to one tile a
+  // wave where that leaves some of the 768 places (three blocks to a CU) empty
+  const int nt = ((dec_logits ? N : K) + 31) / 32;
+  int want = (768 + n_inst - 1) / n_inst;
+  want = want < nt / 4 ? want : nt / 4;
+  want = want > nt / 32 ? want : nt / 32;
+  const int tiles = want > 1 ? (nt + want - 1) / want : nt;
+  const int bpi = (nt + tiles - 1) / tiles;
+  const unsigned grid = (unsigned)(n_inst * bpi);
   if (dtype == VASE_BF16) {
-    // blocks of at least 32 tiles (8 a wave, over which the operands' staging is
-    // spread), evenly split, so that no block is a remainder; down to one tile a
-    // wave where that leaves some of the 768 places (three blocks to a CU) empty
-    const int nt = ((dec_logits ? N : K) + 31) / 32;
-    int want = (768 + n_inst - 1) / n_inst;
-    want = want < nt / 4 ? want : nt / 4;
-    want = want > nt / 32 ? want : nt / 32;
-    const int tiles = want > 1 ? (nt + want - 1) / want : nt;
-    const int bpi = (nt + tiles - 1) / tiles;
     const uint16_t* qd = static_cast<const uint16_t*>(q_dec);
-    const unsigned grid = (unsigned)(n_inst * bpi);
-    const uint16_t* kk = static_cast<const uint16_t*>(k);
-    const uint16_t* vv = static_cast<const uint16_t*>(v);
-    if (d == 128)
-      hipLaunchKernelGGL((dkv_score_mfma_kernel<128>), dim3(grid), dim3(kDkvBlock), 0, stream, kk,
-                         vv, g, N, K, r, bpi, tiles, out, qd, G, dec_logits);
-    else
-      hipLaunchKernelGGL((dkv_score_mfma_kernel<64>), dim3(grid), dim3(kDkvBlock), 0, stream, kk,
-                         vv, g, N, K, r, bpi, tiles, out, qd, G, dec_logits);
+    auto kernel = d == 128 ? dkv_score_mfma_kernel<128> : dkv_score_mfma_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kDkvBlock), 0, stream,
+                       static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), g, N, K, r,
+                       bpi, tiles, out, qd, G, dec_logits);
   } else {
-    const dim3 grid((K + kDkvBlock - 1) / kDkvBlock, n_inst);
-    const float* kk = static_cast<const float*>(k);
-    const float* vv = static_cast<const float*>(v);
-    if (d == 128)
-      hipLaunchKernelGGL((dkv_score_valu_kernel<128>), grid, dim3(kDkvBlock), 0, stream, kk, vv, g,
-                         N, K, r, out);
-    else
-      hipLaunchKernelGGL((dkv_score_valu_kernel<64>), grid, dim3(kDkvBlock), 0, stream, kk, vv, g,
-                         N, K, r, out);
+    auto kernel = d == 128 ? dkv_score_f32_kernel<128> : dkv_score_f32_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kDkvBlock), 0, stream, static_cast<const float*>(k),
+                       static_cast<const float*>(v), g, N, K, r, bpi, tiles, out);
   }
   return hipGetLastError();
 }

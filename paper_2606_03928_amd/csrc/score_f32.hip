@@ -21,7 +21,7 @@
 // pass 1, so they cost no launch and their memory time overlaps with MFMA work.
 // Against one thread per row with LDS operands and scalar fma (two LDS reads
 // per product, 160-key runs of one wave each), 24 instances of 96 window rows
-// and 1092 slots at d = 128 went from 371 to F32_US us.
+// and 1092 slots at d = 128 went from 371 to 32 us.
 #include "vase_internal.hpp"
 #include "vase.h"
 

@@ -43,3 +43,25 @@ def test_dkv_score_blocks(n, K, B, d, G, r):
     ld = torch.bmm(q.double(), k.double().transpose(1, 2).contiguous())
     ab = torch.bmm(q.double().abs(), k.double().abs().transpose(1, 2).contiguous())
     assert ((logits.double() - ld).abs() <= (d + 1) * 2.0 ** -24 * ab).all()
+
+
+@pytest.mark.parametrize("n,K,B,d,r", [
+    (1, 1, 1, 64, 1), (2, 33, 1, 128, 32), (8, 2000, 48, 64, 20), (400, 1030, 10, 128, 31),
+    (800, 1100, 5, 64, 17),
+])
+def test_dkv_score_f32_blocks(n, K, B, d, r):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n + K)
+    k, v = (torch.randn((n, K + B, d), generator=gen, device=DEV) for _ in range(2))
+    g = vase.dkv_projection(n, d, 7, 3, r=r)
+    score = vase.dkv_score(k, v, g, K, B)
+    kd, vd = k[:, :K].double(), v[:, :K].double()
+    want = torch.bmm(kd, g.double()).square().sum(-1) * torch.bmm(vd, g.double()).square().sum(-1)
+    # as above with one fp32 sum per projection
+    eps = (d + 1) * 2.0 ** -24
+    rel = sum(2 * eps * torch.bmm(x.abs(), g.double().abs()).norm(dim=-1) /
+              torch.bmm(x, g.double()).norm(dim=-1) for x in (kd, vd)) + (r + 4) * 2.0 ** -23
+    assert ((score.double() - want).abs() <= 1.5 * rel * want).all()
+    # an infinite element makes its row's score infinite, not a NaN of the padding
+    k[0, 0, d - 1] = float("inf")
+    assert vase.dkv_score(k, v, g, K, B)[0, 0].item() == float("inf")
