@@ -948,31 +948,6 @@ __global__ __launch_bounds__(NT) void score_pool_map_kernel(
   }
 }
 
-// ---------------------------------------------------------------------------
-// value score of each of the K candidate value rows: Range, L2 or Var as in
-// chunk_value (the stable compaction's, when it is not fused with the decode)
-// ---------------------------------------------------------------------------
-
-template <typename T, int D>
-__global__ __launch_bounds__(kSBlock) void value_kernel(const T* __restrict__ v, int N, int K,
-                                                      int kind, float* __restrict__ out,
-                                                      uint32_t* __restrict__ status) {
-  constexpr int VEC = Vec16<T>::n;
-  constexpr int LPR = D / VEC;
-  constexpr int RPB = kSBlock / LPR;
-  const int inst = blockIdx.y;
-  const int row = blockIdx.x * RPB + threadIdx.x / LPR;
-  const int seg = threadIdx.x % LPR;
-  const bool ok = row < K;
-  const int rr = ok ? row : K - 1;
-  const uint4 w = reinterpret_cast<const uint4*>(v + ((size_t)inst * N + rr) * D)[seg];
-  float f[VEC];
-  Vec16<T>::unpack(w, f);
-  const float val = row_value_score<VEC, LPR>(f, kind);
-  if (ok && seg == 0) out[(size_t)inst * K + row] = val;
-  if (status) block_status(status, ok && any_nonfinite<VEC>(f), VASE_STATUS_VALUE_ROW);
-}
-
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 template <int D, int W, bool P>
@@ -1132,25 +1107,6 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
                  ? 0 : pl.off_col + align256((size_t)n_inst * pl.n_slab * K * sizeof(float));
   (void)d;
   return pl;
-}
-
-hipError_t launch_value_rows(const void* v, int dtype, int n_inst, int N, int K, int d, int kind,
-                             float* out, hipStream_t stream, uint32_t* status) {
-  const int lpr = d * (dtype == VASE_BF16 ? 2 : 4) / 16;
-  const int rpb = kSBlock / lpr;
-  const dim3 rg((K + rpb - 1) / rpb, n_inst);
-  if (dtype == VASE_BF16) {
-    if (d == 128) hipLaunchKernelGGL((value_kernel<bf16_t, 128>), rg, dim3(kSBlock), 0, stream,
-                                     static_cast<const bf16_t*>(v), N, K, kind, out, status);
-    else hipLaunchKernelGGL((value_kernel<bf16_t, 64>), rg, dim3(kSBlock), 0, stream,
-                            static_cast<const bf16_t*>(v), N, K, kind, out, status);
-  } else {
-    if (d == 128) hipLaunchKernelGGL((value_kernel<float, 128>), rg, dim3(kSBlock), 0, stream,
-                                     static_cast<const float*>(v), N, K, kind, out, status);
-    else hipLaunchKernelGGL((value_kernel<float, 64>), rg, dim3(kSBlock), 0, stream,
-                            static_cast<const float*>(v), N, K, kind, out, status);
-  }
-  return hipGetLastError();
 }
 
 hipError_t launch_score(const void* k, const void* v, const void* q, int dtype, int n_inst, int K,

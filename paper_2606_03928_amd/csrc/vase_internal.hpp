@@ -243,10 +243,6 @@ hipError_t launch_compact_decode(void* k, void* v, int dtype, int n_inst, int K,
                                  const int32_t* src, const void* q, int G, void* out,
                                  int value_kind, float* vrange, void* ws, const CompactPlan& plan,
                                  hipStream_t stream);
-// value scores (Range, L2 or Var) of rows [0, K) of a [n_inst][N][d] cache
-hipError_t launch_value_rows(const void* v, int dtype, int n_inst, int N, int K, int d, int kind,
-                             float* out, hipStream_t stream, uint32_t* status = nullptr);
-
 constexpr int kPartHead = 4;   // floats ahead of o[d] in a decode partial: m, l, m_p, l_p
 struct DecodePlan {
   int n_split;      // key splits per instance
