@@ -19,9 +19,12 @@
 // hundred is an exact tie, so that some lane of a wave has one in most rows: a
 // branch per element (12 % taken) costs less than one per row with the divides of
 // all eight (250 us for 193, 576 instances of 4096 rows at 4 bits), also with the
-// ties told apart from their residuals first (254 us).  The clamp to
-// [0, 2^b - 1] needs no upper bound: with x - z <= Range (rounding is monotonic)
-// the product stays below 2^b - 1/2.
+// ties told apart from their residuals first (254 us).  The product's code needs
+// no upper bound where Delta is a normal number: with x - z <= Range (rounding is
+// monotonic) the product stays below 2^b - 1/2.  A subnormal Delta is off by up
+// to half its last place whatever its size (Range 16 * 2^-149 at 4 bits: Delta is
+// 2^-149 and the quotient 16), so such groups take the divide, whose codes are
+// clamped on both sides.
 //
 // Layout: a row of D elements is spread over LPR = D*e/16 lanes, 16 bytes each;
 // a group covers GROUP/VEC consecutive lanes, so its min and max are butterfly
@@ -103,15 +106,16 @@ __device__ __forceinline__ uint4 pack16<bf16_t>(const float* r) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// the code of one element (see the file comment for why the fast quotient is
-// safe); inv = 1 / delta, 0 unless delta > 0
-__device__ __forceinline__ float quant_code(float x, float z, float delta, float inv) {
+// the code of one element in [0, levels] (see the file comment for why the fast
+// quotient is safe); inv = 1 / delta, 0 unless delta > 0, and infinite (so that
+// the product is no finite number) where delta is subnormal
+__device__ __forceinline__ float quant_code(float x, float z, float delta, float inv, float levels) {
   const float t = x - z;
   const float u = t * inv;
   float q = __builtin_rintf(u);
   // the maximum also maps a NaN (non-finite inputs) to 0
   if (!(__builtin_fabsf(u - q) <= 0.5f - 0x1p-12f))
-    q = delta > 0.0f ? fmaxf(__builtin_rintf(t / delta), 0.0f) : 0.0f;
+    q = delta > 0.0f ? fminf(fmaxf(__builtin_rintf(t / delta), 0.0f), levels) : 0.0f;
   return q;
 }
 
@@ -179,12 +183,12 @@ __global__ __launch_bounds__(kQBlock) void quant_rows_kernel(
     const float q0 = range * kRcpLevels;
     const float qc = __builtin_fmaf(__builtin_fmaf(-q0, levels, range), kRcpLevels, q0);
     const float delta = q0 < INFINITY ? qc : q0;
-    const float inv = delta > 0.0f ? __builtin_amdgcn_rcpf(delta) : 0.0f;
+    const float inv = delta >= 0x1p-126f ? __builtin_amdgcn_rcpf(delta) : delta > 0.0f ? INFINITY : 0.0f;
     using Packed = typename std::conditional<VEC * BITS <= 32, uint32_t, uint64_t>::type;
     float q[VEC], ss = 0.0f;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      q[e] = quant_code(f[e], gmn, delta, inv);
+      q[e] = quant_code(f[e], gmn, delta, inv, levels);
       const float diff = f[e] - __builtin_fmaf(q[e], delta, gmn);
       ss = __builtin_fmaf(diff, diff, ss);
     }

@@ -73,6 +73,28 @@ def test_quantize_tiny_ranges(dtype, bits, group):
     np.testing.assert_array_equal(q["params"].cpu().numpy(), ref["params"])
     np.testing.assert_array_equal(q["range"].cpu().numpy(), ref["range"])
 
+
+@pytest.mark.parametrize("bits,group,lo,hi", [(2, 32, 1, 40), (4, 32, 4, 218), (4, 128, 4, 218),
+                                              (8, 64, 256, 1000), (8, 128, 256, 65536)])
+def test_quantize_subnormal_steps(bits, group, lo, hi):
+    # groups whose Range is a few times 2^b - 1 units of 2^-149: the step is so
+    # coarsely rounded there that Range / Delta reaches 2^b and beyond, and the
+    # codes must be clamped to 2^b - 1
+    cfg = _cfg("tiny", dtype="f32", d=128)
+    n, N, d = cfg.n_inst, cfg.N, cfg.d
+    g = torch.Generator(device="cpu")
+    g.manual_seed(bits * 1000 + group)
+    span = torch.randint(lo, hi, (n, N, d // group, 1), generator=g)
+    units = (torch.rand((n, N, d // group, group), generator=g) * (span + 1)).long().clamp(max=span)
+    units[..., 0], units[..., 1] = 0, span[..., 0]
+    base = torch.randint(-2000, 2000, (n, N, d // group, 1), generator=g)
+    x = ((units + base).double() * 2.0 ** -149).float().view(n, N, d)
+    q = vase.quantize(x.to(DEV), cfg.K, cfg.B, bits, group, Nv=0)
+    torch.cuda.synchronize()
+    ref = oracle.quantize(x, cfg.K, bits, group, Nv=0)
+    np.testing.assert_array_equal(q["codes"].cpu().numpy(), ref["codes"])
+    np.testing.assert_array_equal(q["params"].cpu().numpy(), ref["params"])
+
 @pytest.mark.parametrize("name,kw,n_inst,bits,group,Nv,sample", CASES)
 def test_quantize_parity(name, kw, n_inst, bits, group, Nv, sample):
     cfg = _cfg(name, **kw)
