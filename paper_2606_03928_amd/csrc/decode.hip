@@ -51,9 +51,9 @@ __device__ __forceinline__ float lse_nat(float m, float l) {
 
 // A decode step's new token: cache row n_valid - 1 (`slot`) takes k_new and v_new,
 // and q_win[inst][g][ring] takes q[inst][g] (byte copies).  The workgroup whose
-// rows include the slot writes them and takes the row itself from k_new and
-// v_new; no other workgroup reads it.  As a launch of its own ahead of the
-// attention this cost 2.5 us and a gap in a step of 16 (8 instances, 2089 rows).
+// rows include the slot writes them; no other workgroup reads the row.  As a
+// launch of its own ahead of the attention this cost 2.5 us and a gap in a step
+// of 16 (8 instances, 2089 rows).
 struct DecAppend {
   const uint4 *k_new, *v_new;   // [n_inst][row]; null: no append
   uint4* q_win;                 // [n_inst][G][w][row]
@@ -94,10 +94,15 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
 
   uint4* kb = reinterpret_cast<uint4*>(k + (size_t)inst * N * D);
   uint4* vb = reinterpret_cast<uint4*>(v + (size_t)inst * N * D);
-  // the appended row's slot: past every row when there is none
-  const int slot = ap.k_new ? n_valid - 1 : n_valid;
-  // its k_new and v_new as offsets from the cache rows
-  const ptrdiff_t kn = ap.k_new + (size_t)inst * LPR - kb, vn = ap.v_new + (size_t)inst * LPR - vb;
+  // The new row is written before the loop, which then reads it like any other
+  // row (of this workgroup, behind the barrier).  The split that holds it covers
+  // only rows from n_persist on and is short, so the detour is off the critical
+  // path; picking k_new or the cache per row inside the loop took a wave of
+  // occupancy at some G (396 instances of 383 rows at G = 6: 67 -> 86 us).
+  if (ap.k_new && split == n_split - 1) {
+    append_rows<kDecBlock>(ap, kb, vb, reinterpret_cast<const uint4*>(q), inst, n_valid - 1, G, LPR);
+    __syncthreads();
+  }
   float qf[G][VEC];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -123,8 +128,8 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
       const int r = r0 + u * RPB + rg;
       ok[u] = r < r_hi;
       const int rr = ok[u] ? r : r_lo;
-      kw[u] = kb[(rr == slot ? kn : (ptrdiff_t)rr * LPR) + seg];
-      vw[u] = vb[(rr == slot ? vn : (ptrdiff_t)rr * LPR) + seg];
+      kw[u] = kb[(size_t)rr * LPR + seg];
+      vw[u] = vb[(size_t)rr * LPR + seg];
     }
     float s[UNROLL][G];
 #pragma unroll
@@ -165,8 +170,6 @@ __global__ __launch_bounds__(kDecBlock) void decode_split_kernel(
     }
   }
 
-  if (slot < n_valid && split == n_split - 1)
-    append_rows<kDecBlock>(ap, kb, vb, reinterpret_cast<const uint4*>(q), inst, slot, G, LPR);
   // merge the RPW row groups of the wave (lane bits above log2(LPR)), fixed order
 #pragma unroll
   for (int off = LPR; off < kWave; off <<= 1) {
