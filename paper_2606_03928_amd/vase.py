@@ -156,6 +156,10 @@ def dtype_code(t: torch.dtype) -> int:
     raise VaseError("dtype %s" % t, ERR_DTYPE)
 
 
+# not a documented function of torch, so it may be missing
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _ptr(t: Optional[torch.Tensor]):
     # an int: the functions' argtypes make a pointer of it
     return None if t is None else t.data_ptr()
@@ -164,9 +168,11 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream_ptr(device: torch.device, stream: Optional[torch.cuda.Stream]):
     if stream is not None:
         return stream.cuda_stream
-    # the current stream's handle without a Stream object around it
+    # the current stream's handle, where torch hands it out without a Stream object around it
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
     index = device.index
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+    return _raw_stream(torch.cuda.current_device() if index is None else index)
 
 
 def _status_ptr(status: Optional[torch.Tensor], device):
@@ -188,7 +194,9 @@ def _dev(t: torch.Tensor, name: str) -> None:
     _require(t.is_contiguous(), "%s must be contiguous" % name)
 
 
-@functools.lru_cache(maxsize=256)   # a function of the sizes alone, asked on every call
+# a function of the sizes alone, asked on every call; typed, so that a float that
+# equals a size asked for before is still refused
+@functools.lru_cache(maxsize=256, typed=True)
 def workspace_bytes(op: int, dtype: torch.dtype, n_inst: int, K: int, B: int, d: int,
                     G: int = 1, w: int = 1) -> int:
     return int(load().vase_workspace_bytes(op, dtype_code(dtype), n_inst, K, B, d, G, w))

@@ -310,6 +310,16 @@ def test_workspace_sizes(lib):
     assert vase.workspace_bytes(vase.OP_DECODE, torch.bfloat16, 8, 2048, 128, 128, 4) > 0
 
 
+def test_workspace_sizes_take_whole_numbers_only(lib):
+    # also once the same size has been asked for as an int
+    import ctypes
+    import torch
+    sizes = (2, 128, 32, 64, 2, 8)
+    assert vase.workspace_bytes(vase.OP_SCORE, torch.float32, *sizes) > 0
+    with pytest.raises(ctypes.ArgumentError):
+        vase.workspace_bytes(vase.OP_SCORE, torch.float32, *map(float, sizes))
+
+
 def _score_map(lib, **kw):
     a = dict(k=FAKE, v=FAKE, q=FAKE, lse=None, ord=FAKE, dtype=0, n=4, K=256, B=32, d=128, G=2,
              w=16, pool=7, kind=vase.VALUE_RANGE, attn=FAKE, vr=FAKE, qd=None, dl=None, ws=FAKE,
