@@ -603,6 +603,14 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     // smallest row maximum over the first chunk (rows >= R left out), taken
     // from chunk 0's products when the stream has computed them
     float mb[2] = {0.f, 0.f};
+    // a pass of its own sums the first chunk's terms apart, element j's in l_first:
+    // where they outweigh the rest (a row that looks at the first tokens), every
+    // later term would be rounded to their last place.  One sum, not the 32 terms
+    // of a lane: those took the registers of d = 128 past 256 (7 to 39 spilled in
+    // 10 of 12 instantiations).  Errors against 64 bits, mean of 30 inputs: 64
+    // instances of 4224 slots 1.9e-7 either way, 8 of 2176 1.9e-7 for 2.0e-7
+    constexpr bool kApart = MODE == kPass1;
+    float l_first = 0.f;
     auto init1 = [&](f32x16_t (&a)[2]) {
       const bool ok = lo1 + j < hi1;
       float t[32];
@@ -622,32 +630,27 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
       const float mid = hi == -INFINITY ? 0.f : 0.5f * (hi + lo);
       mb[0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mid), 0));
       mb[1] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mid), 16));
+      if (kApart) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            t[f * 16 + r] = ok ? fast_exp2(__builtin_fmaf(a[f][r], c, -mb[f])) : 0.f;
+        l_first = treduce32<false>(t, lane);
+      }
     };
     float l[32];
 #pragma unroll
     for (int i = 0; i < 32; ++i) l[i] = 0.f;
-    // a pass of its own keeps the first chunk's terms apart: where they outweigh
-    // the rest (a row that looks at the first tokens), every later term would be
-    // rounded to their last place.  64 instances of 4224 slots: error against 64
-    // bits 2.3e-7 -> 1.9e-7 (2.1e-7 with 15 short ranges), 81 -> 83 us
-    constexpr bool kApart = MODE == kPass1;
-    constexpr int kFirst = kApart ? 32 : 1;
-    float l_first[kFirst] = {};
     auto epi1 = [&](int ch, f32x16_t (&a)[2]) {
-      const float okf = lo1 + kChunk * ch + j < hi1 ? 1.f : 0.f;
+      const bool ok = lo1 + kChunk * ch + j < hi1 && (!kApart || ch > 0);
+      const float okf = ok ? 1.f : 0.f;
 #pragma unroll
       for (int f = 0; f < 2; ++f)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           l[f * 16 + r] = __builtin_fmaf(okf, fast_exp2(__builtin_fmaf(a[f][r], c, -mb[f])),
                                          l[f * 16 + r]);
-      if (kApart && ch == 0) {
-#pragma unroll
-        for (int i = 0; i < kFirst; ++i) {
-          l_first[i] = l[i];
-          l[i] = 0.f;
-        }
-      }
     };
     auto side1 = [&](int ch) {
       if (DL != 0 && dl && ch < nc1 && wave == ch % W) {
@@ -670,11 +673,7 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
         dl[(size_t)g * N + lo1 + t] = dls[g * dl_stride + t];
       }
     }
-    if (kApart) {
-#pragma unroll
-      for (int i = 0; i < kFirst; ++i) l[i] += l_first[i];
-    }
-    float lj = treduce32<false>(l, lane);
+    float lj = treduce32<false>(l, lane) + l_first;
     float mj = j < 16 ? mb[0] : mb[1];
     const int row = row_base + elem_row(j, half);
     // Exact as long as every term stays finite and the largest term of each row
