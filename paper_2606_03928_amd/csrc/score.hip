@@ -733,10 +733,10 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
       if (lse_win) l2 = add_persistent(l2, lse_win[(size_t)inst * R + row]);
       row_bad = split == 0 && !(l2 > -INFINITY && l2 < INFINITY);
     }
-    rowbuf[wave][half][j] = l2;
-    __syncthreads();
+    // passed on by lane exchanges: 1 KB more of LDS (rowbuf) would leave a CU one
+    // workgroup for two from 1632 slots per range on, for 1760 (4 waves, d = 128)
 #pragma unroll
-    for (int i = 0; i < 32; ++i) rs[i] = rowbuf[wave][half][i];
+    for (int i = 0; i < 32; ++i) rs[i] = __shfl(l2, 32 * half + i, kWave);
   }
 
   // ---- pass 2: column sums over the slab's rows for slots [key_lo, hi2)
