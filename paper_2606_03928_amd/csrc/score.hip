@@ -898,45 +898,53 @@ __global__ __launch_bounds__(NT) void score_pool_map_kernel(
   const int inst = blockIdx.x;
   const size_t base = (size_t)inst * K;
   const float fr = (float)R, fp = (float)pool;
-  int o[kPoolMapPer];
+  // candidates past the last read the last one's, so that no load is behind a
+  // branch and a thread's loads are all in flight
+  int at[kPoolMapPer], o[kPoolMapPer];
 #pragma unroll
   for (int u = 0; u < kPoolMapPer; ++u) {
-    const int i = threadIdx.x + u * NT;
-    o[u] = i < K ? min(max(ord[base + i], 0), K - 1) : 0;
+    at[u] = min((int)threadIdx.x + u * NT, K - 1);
+    o[u] = ord[base + at[u]];
   }
-  float s[kPoolMapPer];
+  float s[kPoolMapPer], vr[kPoolMapPer];
 #pragma unroll
-  for (int u = 0; u < kPoolMapPer; ++u) s[u] = 0.f;
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    s[u] = 0.f;
+    vr[u] = vr_slot ? vr_slot[base + at[u]] : 0.f;
+  }
   for (int sl = 0; sl < n_slab; ++sl) {
     const float* c = col + ((size_t)inst * n_slab + sl) * K;
 #pragma unroll
+    for (int u = 0; u < kPoolMapPer; ++u) s[u] += c[at[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) {
+    o[u] = min(max(o[u], 0), K - 1);
+    if ((int)threadIdx.x + u * NT < K) slot_v[threadIdx.x + u * NT] = s[u] / fr;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u)
+    if ((int)threadIdx.x + u * NT < K) rank_v[threadIdx.x + u * NT] = slot_v[o[u]];
+  __syncthreads();
+  // the box filter, its taps in order, the thread's candidates side by side
+  const int h = pool / 2;
+#pragma unroll
+  for (int u = 0; u < kPoolMapPer; ++u) s[u] = 0.f;
+  for (int t = -h; t <= h; ++t) {
+#pragma unroll
     for (int u = 0; u < kPoolMapPer; ++u) {
-      const int i = threadIdx.x + u * NT;
-      if (i < K) s[u] += c[i];
+      const int i = at[u] + t;
+      const float x = rank_v[min(max(i, 0), K - 1)];
+      s[u] += i >= 0 && i < K ? x : 0.f;
     }
   }
 #pragma unroll
   for (int u = 0; u < kPoolMapPer; ++u) {
     const int i = threadIdx.x + u * NT;
-    if (i < K) slot_v[i] = s[u] / fr;
-    s[u] = vr_slot && i < K ? vr_slot[base + i] : 0.f;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kPoolMapPer; ++u) {
-    const int i = threadIdx.x + u * NT;
-    if (i < K) rank_v[i] = slot_v[o[u]];
-  }
-  __syncthreads();
-  const int h = pool / 2;
-#pragma unroll
-  for (int u = 0; u < kPoolMapPer; ++u) {
-    const int i = threadIdx.x + u * NT;
     if (i >= K) continue;
-    if (vr_slot) slot_v[i] = s[u];
-    float sum = 0.f;
-    for (int t = i - h; t <= i + h; ++t) sum += t >= 0 && t < K ? rank_v[t] : 0.f;
-    attn[base + i] = sum / fp;
+    if (vr_slot) slot_v[i] = vr[u];
+    attn[base + i] = s[u] / fp;
   }
   if (!vr_slot) return;
   __syncthreads();
@@ -945,6 +953,37 @@ __global__ __launch_bounds__(NT) void score_pool_map_kernel(
     const int i = threadIdx.x + u * NT;
     if (i < K) vrange[base + i] = slot_v[o[u]];
   }
+}
+
+// The same by one workgroup per 256 ranks, which gathers the slots' sums and value
+// scores straight from memory: a scattered 4-byte read each, but no workgroup
+// goes over a whole instance.
+__global__ __launch_bounds__(kSBlock) void score_pool_gather_kernel(
+    const float* __restrict__ col, const int32_t* __restrict__ ord,
+    const float* __restrict__ vr_slot, int K, int n_slab, int R, int pool,
+    float* __restrict__ attn, float* __restrict__ vrange) {
+  __shared__ float mean[kSBlock + 256];   // ranks [i0 - h, i0 + kSBlock + h), h <= 127
+  const int inst = blockIdx.y, i0 = blockIdx.x * kSBlock, h = pool / 2;
+  const size_t base = (size_t)inst * K;
+  const float fr = (float)R, fp = (float)pool;
+  const float* c = col + (size_t)inst * n_slab * K;
+  for (int t = threadIdx.x; t < kSBlock + 2 * h; t += kSBlock) {
+    const int i = i0 - h + t;
+    float s = 0.f;
+    if (i >= 0 && i < K) {
+      const int o = min(max(ord[base + i], 0), K - 1);
+      for (int sl = 0; sl < n_slab; ++sl) s += c[(size_t)sl * K + o];
+    }
+    mean[t] = s / fr;
+  }
+  const int i = i0 + threadIdx.x;
+  const float vr = vr_slot && i < K ? vr_slot[base + min(max(ord[base + i], 0), K - 1)] : 0.f;
+  __syncthreads();
+  if (i >= K) return;
+  float sum = 0.f;
+  for (int t = 0; t < pool; ++t) sum += mean[threadIdx.x + t];
+  attn[base + i] = sum / fp;
+  if (vr_slot) vrange[base + i] = vr;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1135,15 +1174,22 @@ hipError_t launch_score(const void* k, const void* v, const void* q, int dtype, 
   const float* col = reinterpret_cast<const float*>(wsb + pl.off_col);
   if (!pl.pool_in_kernel) {
     if (ord) {
-      // 8 candidates per thread: four waves cover K <= 2048, sixteen the rest
       const float* vs = value_kind <= VASE_VALUE_VAR ? vr_slot : nullptr;
-      const size_t lds = 2 * sizeof(float) * (size_t)K;
-      if (K <= 256 * kPoolMapPer)
-        hipLaunchKernelGGL((score_pool_map_kernel<256>), dim3(n_inst), dim3(256), lds, stream, col,
-                           ord, vs, K, pl.n_slab, R, pool, attn, vrange);
-      else
-        hipLaunchKernelGGL((score_pool_map_kernel<1024>), dim3(n_inst), dim3(1024), lds, stream, col,
-                           ord, vs, K, pl.n_slab, R, pool, attn, vrange);
+      // Up to 2^19 candidates in the call the scattered reads meet in the caches and
+      // more workgroups win, beyond that reading everything once does (score of
+      // the 16-row window with Range, gathered / staged, us): 2 instances of 4096
+      // 16.0 / 21.3, 64: 31.0 / 33.9, 128: 47.0 / 47.1, 256: 79.9 / 75.9
+      if ((long long)n_inst * K <= (1LL << 19)) {
+        hipLaunchKernelGGL(score_pool_gather_kernel, dim3((K + kSBlock - 1) / kSBlock, n_inst),
+                           dim3(kSBlock), 0, stream, col, ord, vs, K, pl.n_slab, R, pool, attn, vrange);
+      } else {
+        // 8 candidates per thread: four waves cover K <= 2048, sixteen the rest
+        const size_t lds = 2 * sizeof(float) * (size_t)K;
+        const bool wide = K > 256 * kPoolMapPer;
+        hipLaunchKernelGGL(wide ? score_pool_map_kernel<1024> : score_pool_map_kernel<256>, dim3(n_inst),
+                           dim3(wide ? 1024 : 256), lds, stream, col, ord, vs, K, pl.n_slab, R, pool,
+                           attn, vrange);
+      }
     } else {
       hipLaunchKernelGGL(score_pool_kernel, dim3((K + kPoolTile - 1) / kPoolTile, n_inst),
                          dim3(kSBlock), 0, stream, col, K, pl.n_slab, R, pool, attn);

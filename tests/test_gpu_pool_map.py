@@ -17,14 +17,29 @@ def _lib(gpu_lib):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("K,pool", [(1, 255), (255, 1), (257, 7), (2048, 255), (2049, 7), (8191, 31),
-                                    (8192, 7)])
-@pytest.mark.parametrize("dtype,rows", [(torch.bfloat16, 24), (torch.bfloat16, 700),
-                                        (torch.float32, 24)])
+SIZES = [(1, 255), (255, 1), (257, 7), (2048, 255), (2049, 7), (8191, 31), (8192, 7)]
+
+
+# the launch does not depend on the cache type; the small sizes cover fp32
+@pytest.mark.parametrize("K,pool,dtype,rows", [
+    (K, pool, dtype, rows)
+    for dtype, rows in ((torch.bfloat16, 24), (torch.bfloat16, 700), (torch.float32, 24))
+    for K, pool in SIZES if dtype == torch.bfloat16 or K <= 2049])
 def test_pooling_through_the_map(K, pool, dtype, rows):
-    if dtype == torch.float32 and K > 2049:
-        pytest.skip("the launch does not depend on the cache type; the small sizes cover fp32")
-    n, B, d = 3, 9, 64
+    _check(3, K, pool, dtype, rows)
+
+
+@pytest.mark.parametrize("n,K,pool,rows", [
+    # beyond 2^19 candidates one workgroup holds an instance: the last call of the
+    # other launch, four and sixteen waves, candidates per thread that do not divide
+    (64, 8192, 31, 24), (65, 8192, 255, 24), (65, 8191, 7, 24), (257, 2048, 7, 24),
+    (257, 2049, 1, 24), (600, 1001, 13, 520), (2100, 255, 255, 520)])
+def test_pooling_of_many_candidates(n, K, pool, rows):
+    _check(n, K, pool, torch.bfloat16, rows)
+
+
+def _check(n, K, pool, dtype, rows):
+    B, d = 9, 64
     g = torch.Generator(device="cpu")
     g.manual_seed(K + pool + rows)
     k, v = (torch.randn((n, K + B, d), generator=g).to(dtype).to(DEV) for _ in range(2))
