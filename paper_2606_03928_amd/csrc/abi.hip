@@ -30,16 +30,12 @@ int hip_status(hipError_t e) { return e == hipSuccess ? VASE_OK : VASE_ERR_HIP; 
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// score under an order map: the score's own workspace, then room for two fp32
-// per slot (the value scores per slot, which the pooling puts into temporal order)
-size_t score_map_phys_offset(int dtype, int n_inst, int K, int B, int d, int G, int w) {
-  return align256(vase::score_plan(dtype, n_inst, K, B, d, G, w).bytes);
-}
-size_t score_map_bytes(int dtype, int n_inst, int K, int B, int d, int G, int w) {
-  const vase::ScorePlan pl = vase::score_plan(dtype, n_inst, K, B, d, G, w);
+// score under an order map: the score's own workspace, then the value scores per
+// slot, which the pooling puts into temporal order (and as much again, unused:
+// the size that callers know)
+size_t score_map_bytes(const vase::ScorePlan& pl, int n_inst, int K) {
   if (pl.bytes == 0) return 0;   // one workgroup per instance pools through the map itself
-  return score_map_phys_offset(dtype, n_inst, K, B, d, G, w) +
-         2 * align256((size_t)n_inst * K * sizeof(float));
+  return align256(pl.bytes) + 2 * align256((size_t)n_inst * K * sizeof(float));
 }
 
 }  // namespace
@@ -75,7 +71,7 @@ size_t vase_workspace_bytes(int op, int dtype, int n_inst, int K, int B, int d, 
       return vase::compact_decode_bytes(dtype, n_inst, K, B, d, G);
     case VASE_OP_SCORE_MAP:
       if (G < 1 || w < 1) return 0;
-      return score_map_bytes(dtype, n_inst, K, B, d, G, w);
+      return score_map_bytes(vase::score_plan(dtype, n_inst, K, B, d, G, w), n_inst, K);
     case VASE_OP_DECODE: {
       if (G < 1) return 0;
       // the decode plan depends on n_valid and n_persist; size for the largest
@@ -118,8 +114,8 @@ int score_common(const void* k_cache, const void* v_cache, const void* q_win, co
   dec.q = q_dec;
   dec.G = G;
   dec.out = dec_logits;
-  const vase::ScorePlan plan = vase::score_plan(dtype, n_inst, K, B, d, G, w);
-  const size_t need = ord ? score_map_bytes(dtype, n_inst, K, B, d, G, w) : plan.bytes;
+  const vase::ScorePlan plan = vase::score_plan(dtype, n_inst, K, B, d, G, w, lse_win != nullptr);
+  const size_t need = ord ? score_map_bytes(plan, n_inst, K) : plan.bytes;
   if (need > 0 && (!ws || ws_bytes < need || !aligned16(ws))) return VASE_ERR_WORKSPACE;
   const long long blocks = (long long)n_inst * plan.n_slab * (plan.n_chunk1 > plan.n_chunk2 ? plan.n_chunk1 : plan.n_chunk2);
   if (blocks > 0x7fffffffLL) return VASE_ERR_UNSUPPORTED;
@@ -128,8 +124,7 @@ int score_common(const void* k_cache, const void* v_cache, const void* q_win, co
   // the same way (random ones are drawn per temporal rank directly)
   float* vr_phys = nullptr;
   if (ord && !plan.pool_in_kernel)
-    vr_phys = reinterpret_cast<float*>(static_cast<char*>(ws) +
-                                       score_map_phys_offset(dtype, n_inst, K, B, d, G, w));
+    vr_phys = reinterpret_cast<float*>(static_cast<char*>(ws) + align256(plan.bytes));
   hipError_t e = vase::launch_score(k_cache, v_cache, q_win, dtype, n_inst, K, B, d, G, w, pool,
                                     value_kind, lse_win, attn_out, vrange_out, ws, plan, s, ord,
                                     dec, status, vr_phys);

@@ -429,6 +429,20 @@ __device__ __forceinline__ float merge_parts(const float2* p, int R, int n_part)
 
 enum ScoreMode { kPass1 = 0, kPass2 = 1, kFused = 2 };
 
+// Workgroups of score_mfma_kernel that a CU holds: 160 KB of LDS in steps of 1280
+// bytes (the ring, the rows' and columns' exchange, 256 for the block votes, and
+// what the launch adds), and 512 registers to a lane of a SIMD, of which the
+// second pass takes 165 at d = 64 and every other one more than 170.
+int score_places(int d, int waves, ScoreMode mode, size_t dynamic) {
+  if (waves == 8) return 1;
+  size_t lds = (size_t)kRingChunks * kChunk * d * 2 + 256 + dynamic;
+  if (mode != kPass2) lds += (size_t)waves * 2 * 32 * 4;
+  if (mode != kPass1) lds += (size_t)4 * kChunk * waves * 4;
+  const size_t n = (size_t)160 * 1024 / ((lds + 1279) / 1280 * 1280);
+  const size_t most = d == 64 && mode == kPass2 ? 3 : 2;
+  return n < 1 ? 1 : n > most ? (int)most : (int)n;
+}
+
 // The ring and the stream state of one pass.  A pass that scores values (pass
 // 2 with Range, L2 or Var) streams the V rows through a second ring of the
 // same depth S = 4 beside the K ring; every other pass gives the whole LDS
@@ -1067,34 +1081,70 @@ int split_ranges(int N, int n_split) {
   return (N + keys - 1) / keys;
 }
 
-// Ranges per (instance, slab) for `base` of them, few enough that the chip is
-// not full.  A pass takes rounds of 256 CUs (two workgroups of four waves to a
-// CU) x (chunks of a range + what a workgroup costs besides: its rows' load,
-// the ring's fill, the reductions, about 5 chunks of eight waves or 8 of four),
-// and each range one more partial per row to merge.  64 instances of 132 chunks:
-// 4 ranges in one round 96 us, against 15 in 3.75 rounds 150 us.
-constexpr int kMostMerged = 48;   // more ranges cost more to merge than they save
-int pick_split(long long base, int chunks, int least, int most, int waves) {
-  const long long slots = waves == 8 ? 256 : 512;
-  const double own = waves == 8 ? 5 : 8;
-  const int last = least > kMostMerged ? least : (most < kMostMerged ? most : kMostMerged);
+// What a pass takes on the chip, in us.  A workgroup of four waves leaves room for
+// another on its CU, as far as LDS (and for d = 64 registers) reaches; a chunk
+// step of a CU takes step[n] with n workgroups of four waves, wide with one of
+// eight, and a workgroup costs `own` more steps (its rows' load, the ring's fill,
+// the reductions).  Fitted to 900 drawn calls of up to 511 (instance, slab) pairs
+// at every number of ranges (10 % root mean square).  The ranges so chosen take
+// 0.9 % longer than the best ones in the mean, and 0.71 of the time of splitting
+// every call into about 1024 workgroups (500 other draws: at most 1.06 of it,
+// where two workgroups taken for granted made it up to 1.4).
+struct StepCost {
+  double wide, step[4];
+};
+constexpr StepCost kStep128{0.65, {0, 0.54, 0.76, 0.76}}, kStep64{0.58, {0, 0.39, 0.53, 0.62}};
+constexpr double kOwnWide = 7, kOwn = 4.5;   // chunks per workgroup of eight and of four waves
+constexpr double kSplitLaunch = 7.5;         // the second pass and the pooling as launches of their own
+constexpr double kMergePart = 0.09;          // one more partial per row for every pass-2 workgroup
+constexpr double kPoolInside = 3.2e-3;       // pooling by the fused kernel, per candidate (7 taps)
+constexpr double kValueShare = 0.5;          // what value rows add to a pass 2 (none when carried)
+constexpr int kCus = 256;
+
+double pass_us(long long blocks, int places, int waves, int d, int chunks) {
+  const StepCost& c = d == 128 ? kStep128 : kStep64;
+  if (waves == 8) return (double)((blocks + kCus - 1) / kCus) * c.wide * (chunks + kOwnWide);
+  const long long round = (long long)kCus * places;
+  const long long rest = blocks % round;
+  const double steps = (double)(blocks / round) * c.step[places] +
+                       (rest ? c.step[(rest + kCus - 1) / kCus] : 0.0);
+  return steps * (chunks + kOwn);
+}
+
+// Ranges per (instance, slab) for `base` of them, too few to fill the chip, from
+// `least` to `most`.  The choice hangs on the sizes alone, so that a call with
+// and without value rows, decode logits or an order map sums in the same order.
+int pick_split(long long base, int n_slab, int waves, int d, int K, int B, int least, int most,
+               bool lse) {
+  const int chunks = (K + B + kChunk - 1) / kChunk;
   int best_n = least;
   double best = 0;
-  for (int n = least; n <= last; ++n) {
+  for (int n = least; n <= most;) {
     const int per = (chunks + n - 1) / n;
-    const long long rounds = (base * ((chunks + per - 1) / per) + slots - 1) / slots;
-    const double t = (double)rounds * (per + own) + 0.05 * n;
+    const long long blocks = base * ((chunks + per - 1) / per);
+    const size_t keybuf = 2 * sizeof(float) * (size_t)per * kChunk;
+    const int p1 = n == 1 ? score_places(d, waves, kFused, keybuf) : score_places(d, waves, kPass1, 0);
+    const int p2 = n == 1 ? p1 : score_places(d, waves, kPass2, keybuf);
+    // with the persistent normalisers given, pass 1 is one range over the buffer
+    double t = lse ? pass_us(base, p1, waves, d, (B + kChunk - 1) / kChunk)
+                   : pass_us(blocks, p1, waves, d, per) + kMergePart * n;
+    t += pass_us(blocks, p2, waves, d, per) * (1 + kValueShare);
+    if (n > 1) t += kSplitLaunch;
+    else if (n_slab == 1) t += kPoolInside * K;
     if (n == least || t < best) {
       best = t;
       best_n = n;
     }
+    if (per == 1) break;
+    const int next = (chunks + per - 2) / (per - 1);   // the fewest ranges that are shorter
+    n = next > n ? next : n + 1;
   }
   return best_n;
 }
 
 }  // namespace
 
-ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
+ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w, bool lse) {
   ScorePlan pl{};
   const int N = K + B;
   const int R = G * w;
@@ -1119,7 +1169,8 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
       most = more > n_split ? more : n_split;
     }
     pl.n_chunk2 = split_ranges(N, most);
-    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, chunks, n_split, pl.n_chunk2, pl.waves))
+    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, pl.n_slab, pl.waves, d, K, B, n_split,
+                                                          pl.n_chunk2, lse))
                              : pl.n_chunk2;
     pl.split_keys = ((N + pl.n_chunk1 - 1) / pl.n_chunk1 + kChunk - 1) / kChunk * kChunk;
   } else {
@@ -1143,7 +1194,6 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w) {
                                           align256((size_t)n_inst * R * sizeof(float));
   pl.bytes = pl.n_chunk2 == 1 && pl.n_slab == 1
                  ? 0 : pl.off_col + align256((size_t)n_inst * pl.n_slab * K * sizeof(float));
-  (void)d;
   return pl;
 }
 

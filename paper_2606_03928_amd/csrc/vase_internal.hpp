@@ -181,7 +181,8 @@ struct ScorePlan {
   bool pool_in_kernel;  // bf16, one range and one slab per instance: no pool launch
   size_t off_part, off_col, bytes;
 };
-ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w);
+// lse: for a call with lse_win.  The workspace (bytes, off_col) is the same either way
+ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w, bool lse = false);
 // lse_win (nullable): [n_inst][G*w] natural-log LSE of each window row over
 // the persistent slots [0, K); when given, row statistics cover [K, N) only
 // ord (nullable, K <= VASE_MAX_K): an order map; the scores are then pooled over

@@ -1,5 +1,7 @@
 """What the built kernels take of a CU, read from the metadata of the library's own
-code objects (CPU only)."""
+code objects, and the launch plans that count on it (CPU only)."""
+import ctypes
+import random
 import re
 
 import pytest
@@ -7,6 +9,7 @@ import pytest
 from paper_2606_03928_amd import vase
 
 KIND = {0: "pass1", 1: "pass2", 2: "fused"}
+LDS, LDS_STEP = 160 * 1024, 1280
 
 
 def _kernels():
@@ -54,3 +57,48 @@ def test_score_kernels_take_what_the_plan_counts(kernels):
             assert k[".group_segment_fixed_size"] <= lds
             assert (k[".vgpr_count"] + k[".agpr_count"] + 7) // 8 * 8 * most <= 512
 
+
+class Plan(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_int) for n in ("n_chunk1", "n_chunk2", "n_slab", "rows_per_slab",
+                                             "waves", "split_keys")] +
+                [("mfma", ctypes.c_bool), ("pool_in_kernel", ctypes.c_bool)] +
+                [(n, ctypes.c_size_t) for n in ("off_part", "off_col", "bytes")])
+
+
+def _score_plan():
+    f = vase.load()["_ZN4vase10score_planEiiiiiiib"]   # vase::score_plan of vase_internal.hpp
+    f.restype = Plan
+    f.argtypes = [ctypes.c_int] * 7 + [ctypes.c_bool]
+    return f
+
+
+def test_score_ranges_leave_room_on_the_cu(kernels):
+    # Where too few (instance, slab) pairs fill the chip, a range must not be so
+    # long that its column sums leave a CU one workgroup of four waves for two
+    # while workgroups wait, unless no number of ranges that the workspace holds is
+    # short enough.
+    lds = {k: max(x[".group_segment_fixed_size"] for x in ks)
+           for k, ks in _score_kernels(kernels).items()}
+
+    def places(d, n, N):
+        keys = (-(-N // n) + 31) // 32 * 32
+        need = lds[d, 4, "fused" if n == 1 else "pass2"] + 8 * keys
+        return min(2, LDS // (-(-need // LDS_STEP) * LDS_STEP))
+
+    plan = _score_plan()
+    rng = random.Random(5)
+    sizes = [(250, 4096, 128, 128, 4, 64), (400, 2048, 64, 128, 4, 64), (500, 2048, 64, 128, 2, 100)]
+    for _ in range(3000):
+        sizes.append((rng.randint(1, 511), rng.randint(1500, 6000), rng.randint(1, 256),
+                      rng.choice([64, 128]), rng.randint(1, 8), rng.randint(1, 32)))
+    for n, K, B, d, G, w in sizes:
+        N = K + B
+        p = plan(vase.BF16, n, K, B, d, G, w, False)
+        q = plan(vase.BF16, n, K, B, d, G, w, True)
+        assert (p.bytes, p.off_col, p.n_chunk2) == (q.bytes, q.off_col, q.n_chunk2)
+        for x in (p, q):
+            assert 1 <= x.n_chunk1 <= x.n_chunk2 and x.split_keys * x.n_chunk1 >= N
+            assert x.split_keys * (x.n_chunk1 - 1) < N and x.split_keys % 32 == 0
+        assert p.waves == 4 and p.n_slab == 1
+        if places(d, p.n_chunk1, N) == 1 and n * p.n_chunk1 > 256:
+            assert all(places(d, m, N) == 1 for m in range(p.n_chunk1, p.n_chunk2 + 1)), (n, K, B, d)
