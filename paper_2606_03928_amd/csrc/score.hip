@@ -1015,8 +1015,17 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
                                 4 * kChunk * W * 4;
   constexpr size_t kLdsCap = 160 * 1024 - kStaticLds - 1024;
   const size_t q_lds = (size_t)dec.G * D * 2;
-  const int dl_stride =
-      dec.out && q_lds + (size_t)dec.G * dl_keys * 4 <= kLdsCap && !lse_win ? dl_keys : 0;
+  const size_t keybuf = 2 * sizeof(float) * (size_t)pl.split_keys;
+  const size_t staged = q_lds + (size_t)dec.G * dl_keys * 4;
+  // Staging must not cost the CU a workgroup: 350 instances of 1053 slots and 45
+  // rows at d = 128 take 100 us with staged logits at one workgroup to a CU, 53 with
+  // logits written from the loop at two (42 drawn calls of that kind: 0.52 to 0.93
+  // of the staged time).  At as many workgroups the two are within 4 %.
+  const ScoreMode mode1 = pl.n_chunk1 == 1 ? kFused : kPass1;
+  const size_t floor_lds = pl.n_chunk1 == 1 && keybuf > q_lds ? keybuf : q_lds;
+  const bool stage = staged <= kLdsCap && score_places(D, W, mode1, staged > floor_lds ? staged : floor_lds) ==
+                                              score_places(D, W, mode1, floor_lds);
+  const int dl_stride = dec.out && stage && !lse_win ? dl_keys : 0;
   const size_t dec_lds = dec.out ? q_lds + (size_t)dec.G * dl_stride * 4 : 0;
   const int dl_mode = !dec.out ? 0 : dl_stride > 0 ? 1 : 2;
   float2* part = reinterpret_cast<float2*>(ws + pl.off_part);
@@ -1025,7 +1034,6 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
   const uint4* vv = static_cast<const uint4*>(v);
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   const unsigned grid = (unsigned)(n_inst * pl.n_slab * pl.n_chunk1);
-  const size_t keybuf = 2 * sizeof(float) * (size_t)pl.split_keys;
   if (pl.n_chunk1 == 1) {
     auto fused = dl_mode == 0 ? score_mfma_kernel<D, W, kFused, 0, P>
                  : dl_mode == 1 ? score_mfma_kernel<D, W, kFused, 1, P>

@@ -66,3 +66,28 @@ def test_split_scores(dtype, n, K, B, d, G, w):
     v[n - 1, K - 1, 0] = float("inf")
     vase.score(k, v, q, K, B, pool, status=status)
     assert status.item() == vase.STATUS_ROW_NORM | vase.STATUS_VALUE_ROW
+
+
+@pytest.mark.parametrize("n,K,B,d,G,w", [
+    # logits written from the chunk loop, since staged ones would cost the CU a
+    # workgroup: one range, several ranges, d = 64; and staged ones of long and of
+    # short ranges
+    (350, 1000, 53, 128, 5, 9), (206, 3632, 20, 128, 4, 20), (244, 3001, 18, 64, 7, 18),
+    (30, 700, 40, 128, 3, 40), (300, 260, 31, 64, 8, 31),
+])
+def test_split_scores_with_decode_logits(n, K, B, d, G, w):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + K)
+    k, v = (torch.randn((n, K + B, d), generator=g, device=DEV).to(BF) for _ in range(2))
+    q = torch.randn((n, G, w, d), generator=g, device=DEV).to(BF)
+    qd = torch.randn((n, G, d), generator=g, device=DEV).to(BF)
+    ident = vase.identity_order(n, K, DEV)
+    logits = torch.full((n, G, K + B), float("nan"), device=DEV)
+    a0, v0 = vase.score(k, v, q, K, B, 5, ord=ident)
+    a1, v1 = vase.score(k, v, q, K, B, 5, ord=ident, q_dec=qd, dec_logits=logits)
+    assert torch.equal(a0, a1) and torch.equal(v0, v1)
+    # exact products of bf16 values, d of them summed in fp32
+    for i in range(0, n, 64):
+        qi, kt = qd[i:i + 64].double(), k[i:i + 64].double().transpose(1, 2).contiguous()
+        bound = (d + 1) * 2.0 ** -24 * torch.bmm(qi.abs(), kt.abs())
+        assert ((logits[i:i + 64].double() - torch.bmm(qi, kt)).abs() <= bound).all()
