@@ -1198,8 +1198,7 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w, b
   // one workgroup that holds the instance's every row and slot pools by itself
   pl.pool_in_kernel = pl.n_chunk1 == 1 && pl.n_slab == 1;
   // row partials only where the slots may be split
-  pl.off_col = pl.n_chunk2 == 1 ? 0 : align256((size_t)n_inst * pl.n_chunk2 * R * sizeof(float2)) +
-                                          align256((size_t)n_inst * R * sizeof(float));
+  pl.off_col = pl.n_chunk2 == 1 ? 0 : align256((size_t)n_inst * pl.n_chunk2 * R * sizeof(float2));
   pl.bytes = pl.n_chunk2 == 1 && pl.n_slab == 1
                  ? 0 : pl.off_col + align256((size_t)n_inst * pl.n_slab * K * sizeof(float));
   return pl;
