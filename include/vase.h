@@ -347,7 +347,10 @@ int vase_decode_step_noalloc(void* k_cache, void* v_cache, const void* k_new, co
  *  src               in     [n_inst][K] device int32 survivor map (vase_select)
  *  q                 in     [n_inst][G][d] device, dtype
  *  out               out    [n_inst][G][d] device, dtype
- *  ws, ws_bytes      scratch, >= vase_workspace_bytes(VASE_OP_COMPACT_DECODE, ...)
+ *  ws, ws_bytes      scratch, >= vase_workspace_bytes(VASE_OP_COMPACT_DECODE, ...);
+ *                    with less, down to the larger of what vase_compact and
+ *                    vase_decode_attn (n_valid = K) use, a call of few instances
+ *                    runs in fewer parts
  * Errors: VASE_ERR_INVALID_ARG (G < 1 or > 8, null or unaligned pointer, ...),
  *         VASE_ERR_DTYPE, VASE_ERR_WORKSPACE, VASE_ERR_HIP.
  */

@@ -312,9 +312,14 @@ int vase_compact_decode_ex(void* k_cache, void* v_cache, int dtype, int n_inst, 
   if (!aligned16(k_cache) || !aligned16(v_cache) || !aligned16(src) || !aligned16(q) ||
       !aligned16(out) || (vrange_out && !aligned16(vrange_out)))
     return VASE_ERR_INVALID_ARG;
-  const size_t need = vase::compact_decode_bytes(dtype, n_inst, K, B, d, G);
-  if (need > 0 && (!ws || ws_bytes < need || !aligned16(ws))) return VASE_ERR_WORKSPACE;
-  const vase::CompactPlan plan = vase::compact_decode_plan(dtype, n_inst, K, B, d, G);
+  // the workspace that vase_workspace_bytes asks for, or (fewer parts) at least
+  // what the two calls one after the other would take; two sizes, so that the
+  // order of the sums does not hang on what else a caller keeps in its workspace
+  const size_t least = vase::compact_decode_least(dtype, n_inst, K, B, d, G);
+  if (least > 0 && (!ws || ws_bytes < least || !aligned16(ws))) return VASE_ERR_WORKSPACE;
+  const size_t full = vase::compact_decode_bytes(dtype, n_inst, K, B, d, G);
+  const vase::CompactPlan plan = vase::compact_decode_plan(
+      dtype, n_inst, K, B, d, G, least > 0 && ws_bytes >= full ? full : least);
   return hip_status(vase::launch_compact_decode(k_cache, v_cache, dtype, n_inst, K, B, d, src, q, G,
                                                 out, value_kind, vrange_out, ws, plan,
                                                 static_cast<hipStream_t>(stream)));

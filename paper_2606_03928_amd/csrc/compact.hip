@@ -421,21 +421,30 @@ CompactPlan compact_plan(int dtype, int n_inst, int K, int B, int d) {
   return pl;
 }
 
-size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
+size_t compact_decode_least(int dtype, int n_inst, int K, int B, int d, int G) {
   const CompactPlan cp = compact_plan(dtype, n_inst, K, B, d);
   if (cp.n_part == 1 && K <= kCompactOneMaxK) return 0;
   const size_t dec = decode_plan(dtype, n_inst, K, B, d, G, K, K).bytes;
   return cp.bytes > dec ? cp.bytes : dec;
 }
 
+size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
+  const size_t least = compact_decode_least(dtype, n_inst, K, B, d, G);
+  if (least == 0) return 0;
+  const CompactPlan full = compact_decode_plan(dtype, n_inst, K, B, d, G, SIZE_MAX);
+  return (long long)n_inst * full.n_part <= 256 && full.bytes > least ? full.bytes : least;
+}
+
 // Parts per instance for about 512 workgroups (two to a CU; 256 and 1024 are
 // within 5 % of it from 64 to 576 instances), of at least 256 rows: each part
 // but the last stages up to B rows, which are copied once more.  64 instances of
-// 4096 rows and 128 staged: 58 us with 8 parts, 66 with 16.  As many parts as
-// the workspace of compact_decode_bytes holds.
-CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G) {
+// 4096 rows and 128 staged, kernel time: 58 us with 8 parts, 66 with 16.  As many
+// parts as the workspace holds.  The least that a call may come with holds the
+// staged rows or the partials, which for few staged rows leaves one part to an
+// instance; compact_decode_bytes asks for room for more where that leaves CUs
+// idle (7 instances of 754 rows, B = 20, G = 7: one part 47 us, two 31).
+CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G, size_t room) {
   const size_t row_bytes = (size_t)d * (dtype == VASE_BF16 ? 2 : 4);
-  const size_t room = compact_decode_bytes(dtype, n_inst, K, B, d, G);
   const int want = (512 + n_inst - 1) / n_inst;
   const int most = K / 256 > 0 ? K / 256 : 1;
   CompactPlan pl;

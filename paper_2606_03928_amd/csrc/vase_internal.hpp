@@ -234,12 +234,14 @@ hipError_t launch_compact(void* k, void* v, int dtype, int n_inst, int K, int B,
                           const int32_t* src, void* ws, const CompactPlan& plan,
                           hipStream_t stream);
 
-// Fused compaction + one decode step, split into parts like launch_compact; the
-// plan's workspace never exceeds compact_decode_bytes.
+// Fused compaction + one decode step, split into parts like launch_compact, as
+// many as `room` bytes of workspace hold.  compact_decode_bytes is what a caller
+// is told to bring, compact_decode_least what a call needs.
 // vrange (nullable): value score of kind value_kind of each compacted row [0, K)
 constexpr int kCompactOneMaxK = 16384;   // no workspace for one part of up to so many rows
-CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G);
+size_t compact_decode_least(int dtype, int n_inst, int K, int B, int d, int G);
 size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G);
+CompactPlan compact_decode_plan(int dtype, int n_inst, int K, int B, int d, int G, size_t room);
 hipError_t launch_compact_decode(void* k, void* v, int dtype, int n_inst, int K, int B, int d,
                                  const int32_t* src, const void* q, int G, void* out,
                                  int value_kind, float* vrange, void* ws, const CompactPlan& plan,

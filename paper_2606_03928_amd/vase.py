@@ -444,8 +444,10 @@ def compact_decode(k: torch.Tensor, v: torch.Tensor, src: torch.Tensor, q: torch
     if out is None:
         out = torch.empty_like(q)
     _dev(out, "out")
-    ws = _workspace(ws, workspace_bytes(OP_COMPACT_DECODE, k.dtype, n_inst, K, B, d, G), k.device)
-    wp, wn = _ws_args(ws)
+    nb = workspace_bytes(OP_COMPACT_DECODE, k.dtype, n_inst, K, B, d, G)
+    if ws is None:
+        ws = _workspace(None, nb, k.device)
+    wp, wn = _ws_args(ws)      # less than nb may do as well: the library decides
     if vrange_out is None:
         rc = load().vase_compact_decode(_ptr(k), _ptr(v), dtype_code(k.dtype), n_inst, K, B, d,
                                         _ptr(src), _ptr(q), G, _ptr(out), wp, wn,
@@ -457,6 +459,7 @@ def compact_decode(k: torch.Tensor, v: torch.Tensor, src: torch.Tensor, q: torch
         rc = load().vase_compact_decode_ex(_ptr(k), _ptr(v), dtype_code(k.dtype), n_inst, K, B, d,
                                            _ptr(src), _ptr(q), G, _ptr(out), value_kind,
                                            _ptr(vrange_out), wp, wn, _stream_ptr(k.device, stream))
+    _require(rc != ERR_WORKSPACE or wn >= nb, "workspace too small")
     _check(rc, "vase_compact_decode")
     return out
 

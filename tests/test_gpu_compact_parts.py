@@ -63,3 +63,40 @@ def test_compact_decode_parts(dtype, n, K, B, d, G):
         rel = 2 * (d + 2) * 2.0 ** -24 * sabs + (K + 8) * 2.0 ** -24
         bound = rel * v2[i].double().abs().max() + (2.0 ** -8 if dtype == BF else 2.0 ** -24) * want.abs()
         assert ((out[i].double() - want).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("dtype,n,K,B,d,G", [
+    # the least workspace leaves one part to an instance; fewer parts than the full
+    # one; staged rows that bound the parts either way
+    (BF, 7, 754, 20, 128, 7), (F32, 3, 521, 35, 128, 1), (BF, 8, 2048, 128, 128, 2),
+    (BF, 4, 1100, 300, 64, 8),
+])
+def test_compact_decode_workspaces(dtype, n, K, B, d, G):
+    # the size that vase_workspace_bytes gives, and the larger of what compaction
+    # and decode take one after the other, which has always been enough
+    rng = np.random.default_rng(K)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    src = torch.from_numpy(np.stack([_map(rng, K, B, "random") for _ in range(n)])).to(DEV)
+    k, v = (torch.randn((n, K + B, d), generator=g, device=DEV).to(dtype) for _ in range(2))
+    q = torch.randn((n, G, d), generator=g, device=DEV).to(dtype)
+    idx = src.long()[:, :, None].expand(n, K, d)
+    k2, v2 = k.gather(1, idx), v.gather(1, idx)
+    full = vase.workspace_bytes(vase.OP_COMPACT_DECODE, dtype, n, K, B, d, G)
+    splits = max(1, min(-(-4096 // n), K // 256))
+    least = max(vase.workspace_bytes(vase.OP_COMPACT, dtype, n, K, B, d),
+                n * splits * G * (4 + d) * 4)
+    assert 0 < least <= full
+    outs = []
+    for size in (full, least):
+        ks, vs = k.clone(), v.clone()
+        ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+        outs.append(vase.compact_decode(ks, vs, src, q, K, B, ws=ws).double())
+        assert torch.equal(ks[:, :K], k2) and torch.equal(vs[:, :K], v2)
+    # the same sums in another order, then a rounding to the output type
+    sabs = torch.bmm(q.double().abs(), k2.double().abs().transpose(1, 2).contiguous()).max().item()
+    rel = 4 * (d + 2) * 2.0 ** -24 * sabs / math.sqrt(d) + (K + 8) * 2.0 ** -23
+    bound = rel * v2.double().abs().max() + (2.0 ** -7 if dtype == BF else 2.0 ** -23) * outs[0].abs()
+    assert ((outs[0] - outs[1]).abs() <= bound).all()
+    with pytest.raises(ValueError, match="workspace too small"):
+        vase.compact_decode(k, v, src, q, K, B, ws=torch.empty(least - 16, dtype=torch.uint8, device=DEV))
