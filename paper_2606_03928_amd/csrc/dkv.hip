@@ -247,13 +247,27 @@ hipError_t launch_dkv_score(const void* k, const void* v, const float* g, int dt
                             int K, int B, int d, int r, float* out, const void* q_dec, int G,
                             float* dec_logits, hipStream_t stream) {
   const int N = K + B;
-  // blocks of at least 32 tiles (8 a wave, over which the operands' staging is
-  // spread), evenly split, so that no block is a remainder; down to one tile a
-  // wave where that leaves some of the 768 places (three blocks to a CU) empty
+  // Blocks evenly split, so that none is a remainder, down to one tile a wave.
+  // bf16: up to 384 instances as many as fill the 768 places (three blocks to a
+  // CU) and not a few more, which would run a round by themselves (159 instances
+  // of 3035 rows: 5 blocks each 47.7 us, 4 44.5; 51 of 6787: 16 37.3, 15 30.5);
+  // beyond, two.  Where such blocks are longer than 32 tiles the call runs for many
+  // times a block anyway, and blocks of 8 tiles even out its end (200 instances of
+  // 5049 rows: 4 long blocks each 137 us, 19 118; 477 of 5607: 291 and 270).
+  // fp32, whose blocks stage twice the G: 23 of 6083 rows took 518 us for 373
+  // instances, 5 465; but from 512 instances on two rounds of them (797 of 715 rows,
+  // d = 64: one each 70 us, two 64).
   const int nt = ((dec_logits ? N : K) + 31) / 32;
-  int want = (768 + n_inst - 1) / n_inst;
+  int want;
+  if (dtype == VASE_BF16) {
+    want = n_inst <= 384 ? 768 / n_inst : (768 + n_inst - 1) / n_inst;
+    if (nt > 32 * want) want = nt / 8;
+  } else {
+    const int places = n_inst < 512 ? 768 : 1536;
+    want = (places + n_inst - 1) / n_inst;
+    want = want > nt / 32 ? want : nt / 32;
+  }
   want = want < nt / 4 ? want : nt / 4;
-  want = want > nt / 32 ? want : nt / 32;
   const int tiles = want > 1 ? (nt + want - 1) / want : nt;
   const int bpi = (nt + tiles - 1) / tiles;
   const unsigned grid = (unsigned)(n_inst * bpi);

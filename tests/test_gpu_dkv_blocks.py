@@ -65,3 +65,18 @@ def test_dkv_score_f32_blocks(n, K, B, d, r):
     # an infinite element makes its row's score infinite, not a NaN of the padding
     k[0, 0, d - 1] = float("inf")
     assert vase.dkv_score(k, v, g, K, B)[0, 0].item() == float("inf")
+
+
+@pytest.mark.parametrize("n,K,B,d,G,r", [
+    (200, 2300, 10, 64, 2, 20),          # more than 32 tiles a block: blocks of 8 tiles, the last of one
+    (385, 2049, 15, 64, 1, 8),           # two blocks would do without the last tile
+    (384, 2100, 12, 64, 3, 32),          # the last number of instances with whole rounds of blocks
+])
+def test_dkv_score_short_blocks(n, K, B, d, G, r):
+    test_dkv_score_blocks(n, K, B, d, G, r)
+
+
+@pytest.mark.parametrize("n,K,B,d,r", [(512, 700, 3, 64, 8), (511, 700, 3, 64, 20)])
+def test_dkv_score_f32_rounds(n, K, B, d, r):
+    # two rounds of blocks from 512 instances on
+    test_dkv_score_f32_blocks(n, K, B, d, r)
