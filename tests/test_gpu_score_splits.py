@@ -91,3 +91,29 @@ def test_split_scores_with_decode_logits(n, K, B, d, G, w):
         qi, kt = qd[i:i + 64].double(), k[i:i + 64].double().transpose(1, 2).contiguous()
         bound = (d + 1) * 2.0 ** -24 * torch.bmm(qi.abs(), kt.abs())
         assert ((logits[i:i + 64].double() - torch.bmm(qi, kt)).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("n,K,B,G,w", [
+    (520, 1000, 64, 4, 128),     # one workgroup per instance pools by itself
+    (8, 2048, 128, 2, 128),      # split ranges
+    (30, 600, 40, 5, 130),       # two row slabs
+])
+def test_first_round_scores(n, K, B, G, w):
+    # what a whole round selects from, before sampling enters: to the accuracy of a
+    # score call (a round's other outputs hang on which keys were sampled)
+    d, pool = 128, 7
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + K)
+    k, v = (torch.randn((n, K + B, d), generator=g, device=DEV) for _ in range(2))
+    k[:, :4] *= 10
+    k, v = k.to(BF), v.to(BF)
+    q = torch.randn((n, G, w, d), generator=g, device=DEV).to(BF)
+    qd = torch.randn((n, G, d), generator=g, device=DEV).to(BF)
+    want = torch.cat([_reference(k[i:i + 32], v[i:i + 32], q[i:i + 32], K, pool)[0]
+                      for i in range(0, n, 32)])
+    r = vase.Round(n, K, B, d, G, w, BF, DEV, layout="map")
+    r.run(k, v, q, qd, 16, pool, 7, 0, carry=True)
+    err = (r.attn.double() - want).norm() / want.norm()
+    # a row's normaliser is up to 2^7 in base 2, so its fp32 logarithm is off by up to
+    # 2^-18 and a term by 2^-18 ln 2 = 2.6e-6; the means and sums round far less
+    assert err.item() < 3e-6
