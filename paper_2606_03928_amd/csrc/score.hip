@@ -1090,40 +1090,42 @@ int split_ranges(int N, int n_split) {
 }
 
 // What a pass takes on the chip, in us.  A workgroup of four waves leaves room for
-// another on its CU, as far as LDS (and for d = 64 registers) reaches; a chunk
-// step of a CU takes step[n] with n workgroups of four waves, wide with one of
-// eight, and a workgroup costs `own` more steps (its rows' load, the ring's fill,
-// the reductions).  Fitted to 900 drawn calls of up to 511 (instance, slab) pairs
-// at every number of ranges (10 % root mean square).  The ranges so chosen take
-// 0.9 % longer than the best ones in the mean, and 0.71 of the time of splitting
-// every call into about 1024 workgroups (500 other draws: at most 1.06 of it,
-// where two workgroups taken for granted made it up to 1.4).
+// another on its CU, as far as LDS (and for d = 64 registers) reaches.  A chunk
+// step of a CU takes `fixed` (the ring's transfers and barriers) and `rows` for
+// each of its workgroups, as far as their waves hold window rows; eight waves are
+// one workgroup to a CU.  A workgroup costs `own` more steps (its rows' load, the
+// ring's fill, the reductions).  Fitted to 1200 drawn calls of up to 511
+// (instance, slab) pairs at every number of ranges (9 % root mean square).  The
+// ranges so chosen take 1 % longer than the best ones in the mean and 0.72 of the
+// time of splitting every call into about 1024 workgroups, at most 1.06 of it;
+// with two workgroups taken for granted some took 1.5 of it.
 struct StepCost {
-  double wide, step[4];
+  double fixed, rows, own, wide_fixed, wide_rows, wide_own;   // four waves, eight waves
 };
-constexpr StepCost kStep128{0.65, {0, 0.54, 0.76, 0.76}}, kStep64{0.58, {0, 0.39, 0.53, 0.62}};
-constexpr double kOwnWide = 7, kOwn = 4.5;   // chunks per workgroup of eight and of four waves
-constexpr double kSplitLaunch = 7.5;         // the second pass and the pooling as launches of their own
-constexpr double kMergePart = 0.09;          // one more partial per row for every pass-2 workgroup
-constexpr double kPoolInside = 3.2e-3;       // pooling by the fused kernel, per candidate (7 taps)
-constexpr double kValueShare = 0.5;          // what value rows add to a pass 2 (none when carried)
+constexpr StepCost kStep128{0.50, 0.21, 5.3, 0.53, 0.20, 7.5}, kStep64{0.36, 0.16, 5.3, 0.55, 0.07, 6.0};
+constexpr double kSplitLaunch = 6.3;    // the second pass and the pooling as launches of their own
+constexpr double kMergePart = 0.09;     // one more partial per row for every pass-2 workgroup
+constexpr double kPoolInside = 1.5e-3;  // pooling by the fused kernel, per candidate (5 taps)
+constexpr double kValueShare = 0.24;    // value rows in pass 2: they add 0.6, where not carried
 constexpr int kCus = 256;
 
-double pass_us(long long blocks, int places, int waves, int d, int chunks) {
+// filled: the share of a workgroup's waves that hold window rows
+double pass_us(long long blocks, int places, int waves, double filled, int d, int chunks) {
   const StepCost& c = d == 128 ? kStep128 : kStep64;
-  if (waves == 8) return (double)((blocks + kCus - 1) / kCus) * c.wide * (chunks + kOwnWide);
-  const long long round = (long long)kCus * places;
-  const long long rest = blocks % round;
-  const double steps = (double)(blocks / round) * c.step[places] +
-                       (rest ? c.step[(rest + kCus - 1) / kCus] : 0.0);
-  return steps * (chunks + kOwn);
+  if (waves == 8)
+    return (double)((blocks + kCus - 1) / kCus) * (c.wide_fixed + c.wide_rows * filled) * (chunks + c.wide_own);
+  const long long round = (long long)kCus * places, rest = blocks % round;
+  double steps = (double)(blocks / round) * (c.fixed + c.rows * filled * places);
+  if (rest) steps += c.fixed + c.rows * filled * (double)((rest + kCus - 1) / kCus);
+  return steps * (chunks + c.own);
 }
 
 // Ranges per (instance, slab) for `base` of them, too few to fill the chip, from
 // `least` to `most`.  The choice hangs on the sizes alone, so that a call with
 // and without value rows, decode logits or an order map sums in the same order.
-int pick_split(long long base, int n_slab, int waves, int d, int K, int B, int least, int most,
+int pick_split(long long base, int n_slab, int waves, int R, int d, int K, int B, int least, int most,
                bool lse) {
+  const double filled = (double)((R + 63) / 64) / (n_slab * waves);
   const int chunks = (K + B + kChunk - 1) / kChunk;
   int best_n = least;
   double best = 0;
@@ -1134,9 +1136,9 @@ int pick_split(long long base, int n_slab, int waves, int d, int K, int B, int l
     const int p1 = n == 1 ? score_places(d, waves, kFused, keybuf) : score_places(d, waves, kPass1, 0);
     const int p2 = n == 1 ? p1 : score_places(d, waves, kPass2, keybuf);
     // with the persistent normalisers given, pass 1 is one range over the buffer
-    double t = lse ? pass_us(base, p1, waves, d, (B + kChunk - 1) / kChunk)
-                   : pass_us(blocks, p1, waves, d, per) + kMergePart * n;
-    t += pass_us(blocks, p2, waves, d, per) * (1 + kValueShare);
+    double t = lse ? pass_us(base, p1, waves, filled, d, (B + kChunk - 1) / kChunk)
+                   : pass_us(blocks, p1, waves, filled, d, per) + kMergePart * n;
+    t += pass_us(blocks, p2, waves, filled, d, per) * (1 + kValueShare);
     if (n > 1) t += kSplitLaunch;
     else if (n_slab == 1) t += kPoolInside * K;
     if (n == least || t < best) {
@@ -1177,7 +1179,7 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w, b
       most = more > n_split ? more : n_split;
     }
     pl.n_chunk2 = split_ranges(N, most);
-    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, pl.n_slab, pl.waves, d, K, B, n_split,
+    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, pl.n_slab, pl.waves, R, d, K, B, n_split,
                                                           pl.n_chunk2, lse))
                              : pl.n_chunk2;
     pl.split_keys = ((N + pl.n_chunk1 - 1) / pl.n_chunk1 + kChunk - 1) / kChunk * kChunk;
