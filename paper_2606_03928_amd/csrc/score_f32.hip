@@ -55,6 +55,14 @@ struct Frag {
     const int row = min(row0 + lane % 32, n_rows - 1);
     return reinterpret_cast<const f32x4_t*>(rows + (size_t)row * D) + lane / 32;
   }
+  // the same of window rows (at most 2^16), as one 32-bit lane offset from a
+  // uniform base: three registers less than an address
+  __device__ __forceinline__ static const f32x4_t* at_window(const float* rows, int row0, int n_rows,
+                                                             int lane) {
+    const uint32_t row = (uint32_t)min(row0 + lane % 32, n_rows - 1);
+    return reinterpret_cast<const f32x4_t*>(reinterpret_cast<const char*>(rows) +
+                                            (row * (uint32_t)(D * 4) + (uint32_t)(lane / 32) * 16u));
+  }
   __device__ __forceinline__ void load(const f32x4_t* r) {
 #pragma unroll
     for (int i = 0; i < P; ++i) p[i] = r[2 * i];
@@ -66,20 +74,33 @@ struct Frag {
 // the rest of this tile's MFMAs to arrive and takes no registers of its own.
 // ROWS: the streamed tile holds the rows (else the keys).  Element e of lane l
 // is row 8(e/4) + 4(l/32) + e%4, key l%32.
+//
+// d = 128 sums in two chains.  One chain of 64 MFMAs rounds the products more
+// often than the scalar kernel did, and in calls too short to gain from the
+// softmax sums' shorter chains the scores came out up to 15 % further from 64 bits
+// (37 instances of 1059 slots with lse_win, mean of 6 inputs: scalar 3.45e-7, one
+// chain 3.98e-7, two 3.69e-7; 14 drawn calls: two take 0.94 to 1.02 of the time).
+// At d = 64 one chain stays within 8 % of the scalar kernel, and the 16 additions
+// would cost 3 to 5 % of the shorter tile's time.
 template <int D, bool ROWS>
 __device__ __forceinline__ f32x16_t tile_product(const Frag<D>& fixed, Frag<D>& moving,
                                                  const f32x4_t* next) {
-  f32x16_t acc = {};
+  constexpr int kChains = D == 128 ? 2 : 1;
+  f32x16_t acc[kChains] = {};
 #pragma unroll
   for (int i = 0; i < Frag<D>::P; ++i) {
+    f32x16_t& a = acc[i % kChains];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ROWS ? moving.p[i][c] : fixed.p[i][c],
-                                                 ROWS ? fixed.p[i][c] : moving.p[i][c], acc, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_32x32x2f32(ROWS ? moving.p[i][c] : fixed.p[i][c],
+                                               ROWS ? fixed.p[i][c] : moving.p[i][c], a, 0, 0, 0);
     moving.p[i] = next[2 * i];
     __builtin_amdgcn_sched_barrier(0);   // keep the load here, not ahead of the MFMAs
   }
-  return acc;
+  if constexpr (kChains == 1) return acc[0];
+  const f32x16_t sum = acc[0] + acc[kChains - 1];
+  __builtin_amdgcn_sched_barrier(0);     // 16 registers are free before the epilogue takes its own
+  return sum;
 }
 
 __device__ __forceinline__ int tile_row(int e, int half) { return 8 * (e / 4) + 4 * half + e % 4; }
@@ -188,9 +209,11 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_rows_kernel(
 }
 
 // col[inst][slab][key] = sum over the slab's rows of exp2(s * c - lse2_r), with
-// lse2_r merged from the runs (and lse_win's persistent part, when given).
+// lse2_r merged from the runs (and lse_win's persistent part, when given).  168
+// registers at d = 128 are the last that leave a SIMD three waves (two: 933
+// instances of 311 slots and 12 rows 76 -> 81 us).
 template <int D>
-__global__ __launch_bounds__(kFBlock, 2) void score_f32_cols_kernel(
+__global__ __launch_bounds__(kFBlock, D == 128 ? 3 : 2) void score_f32_cols_kernel(
     const float* __restrict__ k, const float* __restrict__ q, const float2* __restrict__ part,
     const float* __restrict__ lse_win, int N, int K, int R, int n_run, int n_slab, int slab_tiles,
     int n_kg, float c, float* __restrict__ col, uint32_t* __restrict__ status) {
@@ -210,7 +233,7 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_cols_kernel(
   Frag<D> a, b;
   if (active) {
     b.load(Frag<D>::at(k + (size_t)inst * N * D, key0, N, lane));
-    a.load(Frag<D>::at(qi, row_lo, R, lane));
+    a.load(Frag<D>::at_window(qi, row_lo, R, lane));
   }
   bool row_bad = false;
   float sum = 0.f;
@@ -242,7 +265,7 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_cols_kernel(
     if (!active) continue;
     for (int r0 = g0; r0 < g1; r0 += kTile) {
       const int next = r0 + kTile < row_hi ? r0 + kTile : r0;
-      const f32x16_t acc = tile_product<D, true>(b, a, Frag<D>::at(qi, next, R, lane));
+      const f32x16_t acc = tile_product<D, true>(b, a, Frag<D>::at_window(qi, next, R, lane));
       float s[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -256,8 +279,10 @@ __global__ __launch_bounds__(kFBlock, 2) void score_f32_cols_kernel(
     }
   }
   sum += __shfl_xor(sum, 32, kWave);
-  if (active && half == 0 && key0 + j < K)
-    col[((size_t)inst * n_slab + slab) * K + key0 + j] = sum;
+  int key = key0;
+  asm volatile("" : "+s"(key));          // formed here, not kept from the loads on
+  if (active && half == 0 && key + j < K)
+    col[((size_t)inst * n_slab + slab) * K + key + j] = sum;
   // every key group merges the same normalisers: one of them reports
   if (status && kg == 0) block_status(status, row_bad, VASE_STATUS_ROW_NORM);
 }

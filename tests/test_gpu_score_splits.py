@@ -117,3 +117,25 @@ def test_first_round_scores(n, K, B, G, w):
     # a row's normaliser is up to 2^7 in base 2, so its fp32 logarithm is off by up to
     # 2^-18 and a term by 2^-18 ln 2 = 2.6e-6; the means and sums round far less
     assert err.item() < 3e-6
+
+
+@pytest.mark.parametrize("n,K,B,G,w,scalar", [
+    (24, 130, 53, 4, 53, 3.25e-7), (37, 991, 68, 3, 68, 3.66e-7),
+])
+def test_f32_scores_with_lse_round_like_scalar_products(n, K, B, G, w, scalar):
+    # With the persistent normalisers given, the products' rounding is not cancelled by
+    # the normaliser's, so these scores show it most.  `scalar` is the error against
+    # float64 (mean of the same 8 inputs) of one thread per row with scalar fma; a
+    # tenth more is what the order of the sums may add (one chain of MFMAs: 3.79e-7
+    # and 4.20e-7)
+    d, pool, errs = 128, 5, []
+    for seed in range(8):
+        g = torch.Generator(device="cpu")
+        g.manual_seed(seed)
+        k = torch.randn((n, K + B, d), generator=g).to(DEV)
+        k[:, :4] *= 10
+        q = torch.randn((n, G, w, d), generator=g).to(DEV)
+        want, lse, _ = _reference(k, k, q, K, pool)
+        attn, _ = vase.score(k, k, q, K, B, pool, lse_win=lse)
+        errs.append(((attn.double() - want).norm() / want.norm()).item())
+    assert sum(errs) / len(errs) <= 1.1 * scalar
