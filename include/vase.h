@@ -537,7 +537,7 @@ int vase_dkv_projection(int n_inst, uint32_t inst_base, int d, int r, uint64_t s
  *                        slot t < N, for vase_compact_decode_map (the pass then
  *                        also reads the B buffer rows); 1 <= G <= 16
  * bf16 caches project with MFMA against a two-term bf16 split of G (relative
- * error of G about 2^-16, fp32 accumulation); fp32 caches use fp32 FMA.  The
+ * error of G about 2^-16, fp32 accumulation); fp32 caches use fp32 MFMA.  The
  * logits are fp32 MFMA sums of the bf16 products (32x32x16 steps, so they may
  * differ in the last bits from the ones vase_compact_decode_map computes from K).
  * Errors: VASE_ERR_INVALID_ARG (also only one of q_dec and dec_logits_out, G out

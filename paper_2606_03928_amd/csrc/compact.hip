@@ -133,12 +133,17 @@ __global__ __launch_bounds__(kCompBlock) void compact_move_kernel(
 // which no store of this or an earlier chunk touches.  The survivor map sits in
 // LDS (kMapRows of it at a time), so no load waits for an index; the three
 // register stages rotate by name, since a stage that is copied to another one
-// has to have arrived first.
+// has to have arrived first.  That holds within a turn of the three-chunk loop:
+// at its head, where the exits from its middle join, the compiler waits for
+// everything (vmcnt(0)), so two steps of three overlap with the loads ahead and
+// the pipeline drains, stores included, once in every three chunks.
 //
-// 64 instances of 4096 rows (d = 128, G = 4, bf16, 268 MB to move): 129 -> 58 us
-// against staging, moving, scoring and decoding in launches of their own, which
-// went over the cache three times; 576 instances 928 -> 565 us; 512 fp32
-// instances 1558 -> 880 us.
+// Against staging, moving, scoring and decoding in launches of their own, which
+// went over the cache three times, a call repeated on the same buffers (d = 128,
+// G = 4, B = 128, with value scores): 64 bf16 instances of 4096 rows (268 MB to
+// move) 129 -> 59 us, 576 934 -> 560, 512 fp32 instances 1555 -> 882.  Kernel
+// times of the 64: staging 7, this kernel 48, combine 4.  From 1024 bf16
+// instances on, which were one part each before too, 2304 take 1953 us either way.
 // ---------------------------------------------------------------------------
 constexpr int kMapRows = 4096;
 
@@ -438,7 +443,7 @@ size_t compact_decode_bytes(int dtype, int n_inst, int K, int B, int d, int G) {
 // Parts per instance for about 512 workgroups (two to a CU; 256 and 1024 are
 // within 5 % of it from 64 to 576 instances), of at least 256 rows: each part
 // but the last stages up to B rows, which are copied once more.  64 instances of
-// 4096 rows and 128 staged, kernel time: 58 us with 8 parts, 66 with 16.  As many
+// 4096 rows and 128 staged, call time: 58 us with 8 parts, 66 with 16.  As many
 // parts as the workspace holds.  The least that a call may come with holds the
 // staged rows or the partials, which for few staged rows leaves one part to an
 // instance; compact_decode_bytes asks for room for more where that leaves CUs

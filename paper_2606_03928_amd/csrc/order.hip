@@ -245,7 +245,9 @@ __global__ __launch_bounds__(kOrdBlock) void compact_map_decode_kernel(
     return t >= M ? K + (t - M) : s;
   };
   // three register stages that rotate by name: one that is copied to another has
-  // to have arrived first (288 fp32 instances of 4096 rows: 390 -> 371 us)
+  // to have arrived first (288 fp32 instances of 4096 rows: 390 -> 371 us).  At the
+  // head of the three-chunk loop, where the exits from its middle join, the compiler
+  // still waits for every load and store: the pipeline drains once in three chunks
   struct Rows {
     uint4 k[kPasses], v[kPasses];
   };

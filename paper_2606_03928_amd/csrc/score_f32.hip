@@ -318,9 +318,13 @@ hipError_t launch_d(const float* k, const float* v, const float* q, int n_inst, 
 // waves' tiles one after the other, so a pass takes about
 // ceil(waves / 1024 SIMDs) x (tiles per wave + the wave's own operand load and
 // reduction, about half a tile).  A run costs every pass-2 block one more
-// partial to merge (R x 8 bytes, about a twentieth of a tile at R = 256), and
-// more than kMaxRuns are not worth that at any size.  `part_bytes`: room for the
-// partials, of which what the runs leave takes the column sums of further slabs.
+// partial to merge (R x 8 bytes, about a twentieth of a tile at R = 256).  Up to
+// 24 runs and 8 slabs: with 64 and 16, calls of up to 8192 candidates take 0.86 to
+// 1.08 of the time (one instance of 8320 slots: 8 rows 44 -> 38 us, 128 rows 50 ->
+// 45; one of 2176 and 512 rows 34 -> 37); a single much longer instance would
+// gain (50128 slots and 32 rows: 173 -> 93 us; one thread per row took 839).
+// `part_bytes`: room for the partials, of which what the runs leave takes the
+// column sums of further slabs.
 void score_f32_split(int n_inst, int N, int K, int R, size_t part_bytes, ScorePlan& pl) {
   constexpr long long kSimds = 1024;
   constexpr int kMaxRuns = 24, kMaxSlabs = 8;

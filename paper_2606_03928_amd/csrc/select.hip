@@ -1,7 +1,7 @@
 // select.hip -- VaSE-AttnV selection (Sec. 3.2 of the paper) on gfx950.
 //
-// One workgroup per head instance (four waves, eight at the largest K), the
-// candidates [0, K) in registers.  Both selections are the exact k-th-largest
+// One workgroup per head instance (one wave up to K = 512, four, or eight beyond
+// K = 6144), the candidates [0, K) in registers.  Both selections are the exact k-th-largest
 // searches of topk.hpp over 32-bit patterns (non-negative fp32 values order
 // like their bit patterns) with an index-ordered tie resolution, so the result
 // is the unique answer under the total orders
