@@ -73,6 +73,8 @@ constexpr int kSlabRowsMax = 64 * kMaxWaves;
 // slots per range: its column sums and Range (8 bytes per slot) share the 160
 // KB of LDS with the ring (64 KB) and the row/column scratch (5 KB)
 constexpr int kMaxSplitKeys = 11264;
+// (instance, slab) pairs below which the slots may be split to fill the chip
+constexpr int kSplitBelow = 512;
 
 template <int D>
 struct QFrag {
@@ -558,7 +560,7 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     const float* __restrict__ lse_win, float2* __restrict__ part, int n_part,
     float* __restrict__ col, float* __restrict__ vrange, float* __restrict__ attn,
     const int32_t* __restrict__ ord, const uint4* __restrict__ qdec, int G_dec,
-    float* __restrict__ dlog, int dl_stride, uint32_t* __restrict__ status) {
+    float* __restrict__ dlog, int dl_stride, int first_apart, uint32_t* __restrict__ status) {
   constexpr int kU4 = ChunkLayout<D>::kU4;
   __shared__ uint4 ring[kRingChunks * kU4];
   __shared__ float rowbuf[W][2][32];
@@ -622,8 +624,12 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
     // later term would be rounded to their last place.  One sum, not the 32 terms
     // of a lane: those took the registers of d = 128 past 256 (7 to 39 spilled in
     // 10 of 12 instantiations).  Errors against 64 bits, mean of 30 inputs: 64
-    // instances of 4224 slots 1.9e-7 either way, 8 of 2176 1.9e-7 for 2.0e-7
-    constexpr bool kApart = MODE == kPass1;
+    // instances of 4224 slots 1.9e-7 either way, 8 of 2176 1.9e-7 for 2.0e-7.
+    // One range does so where the call might have been split (first_apart), so
+    // that the choice of ranges costs no accuracy: 64 instances of 8448 slots and
+    // 2048 rows 1.8e-7, in about 1024 workgroups 2.6e-7, in one sum 5.5e-7.
+    // Everywhere it would cost 0.4 % of the largest calls
+    const bool apart = MODE == kPass1 || first_apart != 0;
     float l_first = 0.f;
     auto init1 = [&](f32x16_t (&a)[2]) {
       const bool ok = lo1 + j < hi1;
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
       const float mid = hi == -INFINITY ? 0.f : 0.5f * (hi + lo);
       mb[0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mid), 0));
       mb[1] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mid), 16));
-      if (kApart) {
+      if (apart) {
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
@@ -657,7 +663,7 @@ __global__ __launch_bounds__(64 * W, 2) void score_mfma_kernel(
 #pragma unroll
     for (int i = 0; i < 32; ++i) l[i] = 0.f;
     auto epi1 = [&](int ch, f32x16_t (&a)[2]) {
-      const bool ok = lo1 + kChunk * ch + j < hi1 && (!kApart || ch > 0);
+      const bool ok = lo1 + kChunk * ch + j < hi1 && (!apart || ch > 0);
       const float okf = ok ? 1.f : 0.f;
 #pragma unroll
       for (int f = 0; f < 2; ++f)
@@ -1041,7 +1047,7 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
     hipLaunchKernelGGL(fused, dim3(grid), dim3(64 * W), keybuf > dec_lds ? keybuf : dec_lds,
                        stream, kk, vv, qq, N, K, R, pl.n_slab, 1, pl.split_keys, c, pool, kind,
                        lse_win, part, 0, col, vrange, attn, ord, qd, dec.G, dec.out, dl_stride,
-                       status);
+                       (int)(!lse_win && (long long)n_inst * pl.n_slab < kSplitBelow), status);
     return;
   }
   // pass 1: every slot range, or one range over the buffer [K, N) when the
@@ -1053,10 +1059,10 @@ void launch_mfma_w(const void* k, const void* v, const void* q, int n_inst, int 
                               : score_mfma_kernel<D, W, kPass1, 2, P>;
   hipLaunchKernelGGL(pass1, dim3((unsigned)(n_inst * pl.n_slab * n1)), dim3(64 * W), dec_lds,
                      stream, kk, vv, qq, N, K, R, pl.n_slab, n1, keys1, c, pool, kind, lse_win,
-                     part, 0, col, vrange, attn, nullptr, qd, dec.G, dec.out, dl_stride, nullptr);
+                     part, 0, col, vrange, attn, nullptr, qd, dec.G, dec.out, dl_stride, 1, nullptr);
   hipLaunchKernelGGL((score_mfma_kernel<D, W, kPass2, 0, P>), dim3(grid), dim3(64 * W), keybuf, stream,
                      kk, vv, qq, N, K, R, pl.n_slab, pl.n_chunk1, pl.split_keys, c, pool, kind,
-                     lse_win, part, n1, col, vrange, attn, nullptr, nullptr, 0, nullptr, 0, status);
+                     lse_win, part, n1, col, vrange, attn, nullptr, nullptr, 0, nullptr, 0, 0, status);
 }
 
 template <int D>
@@ -1173,13 +1179,13 @@ ScorePlan score_plan(int dtype, int n_inst, int K, int B, int d, int G, int w, b
     const int chunks = (N + kChunk - 1) / kChunk;
     int n_split = (N + kMaxSplitKeys - 1) / kMaxSplitKeys;
     int most = n_split;
-    if (base < 512) {
+    if (base < kSplitBelow) {
       const long long want = (1024 + base - 1) / base;
       const int more = (int)(want < chunks ? want : chunks);
       most = more > n_split ? more : n_split;
     }
     pl.n_chunk2 = split_ranges(N, most);
-    pl.n_chunk1 = base < 512 ? split_ranges(N, pick_split(base, pl.n_slab, pl.waves, R, d, K, B, n_split,
+    pl.n_chunk1 = base < kSplitBelow ? split_ranges(N, pick_split(base, pl.n_slab, pl.waves, R, d, K, B, n_split,
                                                           pl.n_chunk2, lse))
                              : pl.n_chunk2;
     pl.split_keys = ((N + pl.n_chunk1 - 1) / pl.n_chunk1 + kChunk - 1) / kChunk * kChunk;

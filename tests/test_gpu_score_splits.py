@@ -139,3 +139,20 @@ def test_f32_scores_with_lse_round_like_scalar_products(n, K, B, G, w, scalar):
         attn, _ = vase.score(k, k, q, K, B, pool, lse_win=lse)
         errs.append(((attn.double() - want).norm() / want.norm()).item())
     assert sum(errs) / len(errs) <= 1.1 * scalar
+
+
+@pytest.mark.parametrize("n,K,B,d,G,w", [(256, 2000, 48, 128, 5, 64), (128, 3000, 64, 128, 8, 100)])
+def test_one_range_is_as_accurate_as_several(n, K, B, d, G, w):
+    # A call that might be split but takes one range, with rows that look at the first
+    # tokens: a single fp32 sum would round every later term to those tokens' last
+    # place (2.6e-7 and 3.3e-7; about 1024 workgroups 2.1e-7)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(n + K)
+    k = torch.randn((n, K + B, d), generator=g)
+    k[:, :4] *= 10
+    k, q = k.to(BF).to(DEV), torch.randn((n, G, w, d), generator=g).to(BF).to(DEV)
+    want = torch.cat([_reference(k[i:i + 16], k[i:i + 16], q[i:i + 16], K, 7)[0]
+                      for i in range(0, n, 16)])
+    attn, _ = vase.score(k, k, q, K, B, 7)
+    err = ((attn.double() - want).norm() / want.norm()).item()
+    assert err < 2.25e-7, err
