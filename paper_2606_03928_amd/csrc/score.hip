@@ -1115,11 +1115,24 @@ constexpr double kPoolInside = 1.5e-3;  // pooling by the fused kernel, per cand
 constexpr double kValueShare = 0.24;    // value rows in pass 2: they add 0.6, where not carried
 constexpr int kCus = 256;
 
-// filled: the share of a workgroup's waves that hold window rows
-double pass_us(long long blocks, int places, int waves, double filled, int d, int chunks) {
+// filled: the share of a workgroup's waves that hold window rows; uneven: full slabs
+// and one that is not.  Workgroups of those differ, so rounds do not end together:
+// a pass takes no less than its work over the CUs and half of a full workgroup.
+// Without that one range looked best for 233 instances of 4869 slots and 609 rows
+// (577 us, three ranges 544; 95 of 760 and 1677 rows 119 and 98).  At d = 64 a
+// workgroup's time hardly depends on its rows, and the rule above does better (51
+// of 7056 slots and 711 rows 173 us, 193 so).
+double pass_us(long long blocks, int places, int waves, double filled, bool uneven, int d, int chunks) {
   const StepCost& c = d == 128 ? kStep128 : kStep64;
-  if (waves == 8)
-    return (double)((blocks + kCus - 1) / kCus) * (c.wide_fixed + c.wide_rows * filled) * (chunks + c.wide_own);
+  if (waves == 8) {
+    const double step = c.wide_fixed + c.wide_rows * filled;
+    double steps = (double)((blocks + kCus - 1) / kCus) * step;
+    if (uneven && blocks > kCus) {
+      const double least = (double)blocks / kCus * step + 0.5 * (c.wide_fixed + c.wide_rows);
+      steps = steps > least ? steps : least;
+    }
+    return steps * (chunks + c.wide_own);
+  }
   const long long round = (long long)kCus * places, rest = blocks % round;
   double steps = (double)(blocks / round) * (c.fixed + c.rows * filled * places);
   if (rest) steps += c.fixed + c.rows * filled * (double)((rest + kCus - 1) / kCus);
@@ -1132,6 +1145,7 @@ double pass_us(long long blocks, int places, int waves, double filled, int d, in
 int pick_split(long long base, int n_slab, int waves, int R, int d, int K, int B, int least, int most,
                bool lse) {
   const double filled = (double)((R + 63) / 64) / (n_slab * waves);
+  const bool uneven = d == 128 && n_slab > 1 && filled < 1;
   const int chunks = (K + B + kChunk - 1) / kChunk;
   int best_n = least;
   double best = 0;
@@ -1142,9 +1156,9 @@ int pick_split(long long base, int n_slab, int waves, int R, int d, int K, int B
     const int p1 = n == 1 ? score_places(d, waves, kFused, keybuf) : score_places(d, waves, kPass1, 0);
     const int p2 = n == 1 ? p1 : score_places(d, waves, kPass2, keybuf);
     // with the persistent normalisers given, pass 1 is one range over the buffer
-    double t = lse ? pass_us(base, p1, waves, filled, d, (B + kChunk - 1) / kChunk)
-                   : pass_us(blocks, p1, waves, filled, d, per) + kMergePart * n;
-    t += pass_us(blocks, p2, waves, filled, d, per) * (1 + kValueShare);
+    double t = lse ? pass_us(base, p1, waves, filled, uneven, d, (B + kChunk - 1) / kChunk)
+                   : pass_us(blocks, p1, waves, filled, uneven, d, per) + kMergePart * n;
+    t += pass_us(blocks, p2, waves, filled, uneven, d, per) * (1 + kValueShare);
     if (n > 1) t += kSplitLaunch;
     else if (n_slab == 1) t += kPoolInside * K;
     if (n == least || t < best) {

@@ -102,3 +102,13 @@ def test_score_ranges_leave_room_on_the_cu(kernels):
         assert p.waves == 4 and p.n_slab == 1
         if places(d, p.n_chunk1, N) == 1 and n * p.n_chunk1 > 256:
             assert all(places(d, m, N) == 1 for m in range(p.n_chunk1, p.n_chunk2 + 1)), (n, K, B, d)
+
+
+def test_uneven_slabs_are_not_left_to_end_apart():
+    # one range of few, unequal workgroups a CU leaves half of the chip waiting for the
+    # last full ones: ranges chosen so that the work evens out
+    plan = _score_plan()
+    for n, K, B, d, G, w in [(233, 4699, 170, 128, 7, 87), (95, 532, 228, 128, 7, 239)]:
+        n_inst_slabs = n * plan(vase.BF16, n, K, B, d, G, w, False).n_slab
+        assert n_inst_slabs < 512
+        assert plan(vase.BF16, n, K, B, d, G, w, False).n_chunk1 > 1
