@@ -1119,7 +1119,7 @@ constexpr int kCus = 256;
 // and one that is not.  Workgroups of those differ, so rounds do not end together:
 // a pass takes no less than its work over the CUs and half of a full workgroup.
 // Without that one range looked best for 233 instances of 4869 slots and 609 rows
-// (577 us, three ranges 544; 95 of 760 and 1677 rows 119 and 98).  At d = 64 a
+// (577 us, three 544), and two for 95 of 760 and 1677 (119 us, one 98).  At d = 64 a
 // workgroup's time hardly depends on its rows, and the rule above does better (51
 // of 7056 slots and 711 rows 173 us, 193 so).
 double pass_us(long long blocks, int places, int waves, double filled, bool uneven, int d, int chunks) {

@@ -104,11 +104,8 @@ def test_score_ranges_leave_room_on_the_cu(kernels):
             assert all(places(d, m, N) == 1 for m in range(p.n_chunk1, p.n_chunk2 + 1)), (n, K, B, d)
 
 
-def test_uneven_slabs_are_not_left_to_end_apart():
-    # one range of few, unequal workgroups a CU leaves half of the chip waiting for the
-    # last full ones: ranges chosen so that the work evens out
-    plan = _score_plan()
-    for n, K, B, d, G, w in [(233, 4699, 170, 128, 7, 87), (95, 532, 228, 128, 7, 239)]:
-        n_inst_slabs = n * plan(vase.BF16, n, K, B, d, G, w, False).n_slab
-        assert n_inst_slabs < 512
-        assert plan(vase.BF16, n, K, B, d, G, w, False).n_chunk1 > 1
+@pytest.mark.parametrize("n,K,B,G,w,ranges", [(233, 4699, 170, 7, 87, 3), (95, 532, 228, 7, 239, 1)])
+def test_ranges_of_uneven_slabs(n, K, B, G, w, ranges):
+    # full slabs and one that is not: their workgroups do not end together.  Measured at
+    # d = 128: 577 us in one range and 544 in three; 119 in two and 98 in one
+    assert _score_plan()(vase.BF16, n, K, B, 128, G, w, False).n_chunk1 == ranges
